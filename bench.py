@@ -49,18 +49,18 @@ def kernel_roofline_table(w) -> dict:
     (bound, amount, unit).  Bytes for HBM-bound kernels, flops for MFMA."""
     n = w.n
     f = build_flops(w)
-    m = np.arange(1, n, dtype=np.float64)
+    m = np.arange(n - 16, 0, -16, dtype=np.float64)  # trailing orders of the band reduction
     return {
-        # lower triangle of the trailing Hermitian matrix (order m), one launch per reflector
-        "k_trd_hemv": ("hbm", float(np.sum(m * (m + 1) / 2) * 16.0), "B"),
+        # per panel of 16 columns: the update of the trailing lower triangle (order m, K = 32;
+        # none before the first panel) and its product with the panel's 16 vectors
+        "k_band_step": ("mfma", float(np.sum(m[1:] * (m[1:] + 1) / 2) * 32 * 8.0
+                                      + np.sum(m * m) * 16 * 8.0), "flop"),
         "k_stage1_real": ("mfma", float(f["stage1"]), "flop"),
         "zgemm_direct_stage2": ("mfma", float(f["stage2"]), "flop"),
         "zgemm_exchange": ("mfma", float(f["exchange"]), "flop"),
         # triangular products of the squared form: n^3 / 2 complex MACs each
         "zgemm_sq_t1": ("mfma", n ** 3 / 2 * 8.0, "flop"),
         "zgemm_sq_s": ("mfma", n ** 3 / 4 * 8.0, "flop"),
-        # trailing updates of the tridiagonalisation (lower triangle): m(m+1)/2 x 64 per panel
-        "zgemm_her2k": ("mfma", float(np.sum(m[::32] * (m[::32] + 1) / 2)) * 64 * 8.0, "flop"),
     }
 
 
@@ -551,9 +551,7 @@ def main() -> int:
                 "frac": ach / peak, "traffic": tr["bytes"] if tr else None,
                 "traffic_unit": "B per launch", "traffic_source": tr["source"] if tr else None,
                 "traffic_note": tr["note"] if tr else (
-                    "no counter summary of this kernel's current source: counter runs of "
-                    "processes that run the Householder sweep ended in a crash or a hang and "
-                    "are not taken" if bound == "hbm"
+                    "no counter summary of this kernel's current source" if bound == "hbm"
                     else None),
                 "launches_per_step": launches / args.steps,
                 "avg_launch_us": total_ms / launches * 1e3,

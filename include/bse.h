@@ -37,8 +37,9 @@
  *      -6   bse_screening: a pivot of the dielectric-matrix inversion is not
  *           positive (non-finite input)
  *    Once `info` is non-zero, the later kernels of the same calls return at
- *    entry, except the per-column kernels of the Householder sweep, which
- *    index no memory by data and run on; outputs are then undefined.
+ *    entry, except the per-column kernels of the Householder sweep of solves
+ *    that form X+Y, which index no memory by data and run on; outputs are then
+ *    undefined.
  */
 #ifndef BSE_H
 #define BSE_H
@@ -327,14 +328,11 @@ bse_status bse_screening(const bse_screen_desc* desc, const double* eps_v, const
  * Problems run on `nbranch` concurrent branches (streams the batch creates
  * at default priority), largest N^3 first, each branch with its own slice of
  * the workspace.  With one branch per problem (nbranch >= nprob) the Cholesky
- * factorisations (Sec. 4.3) and the Householder sweeps of all problems run
- * batched on the capture stream, each launch serving every problem (up to 16
- * per launch), between per-problem stages on the branches; each problem's
- * results are bitwise those of the plain entry points (with the default
- * BSE_TUNE_BATCH_SWEEP choice).  The workspace then also holds a small table
- * (the sweep's grid counts, 4 bytes per unit of problem order, after the
- * branch slices), which bse_batch_capture fills with a blocking host-to-device
- * copy: no replay of the batch may be running during a capture.  All pointers given to bse_batch_capture stay
+ * factorisations (Sec. 4.3) and the reductions to tridiagonal form of all
+ * problems run batched on the capture stream, each launch serving every problem
+ * (up to 16 per launch), between per-problem stages on the branches; each
+ * problem's results are bitwise those of the plain entry points.  All pointers
+ * given to bse_batch_capture stay
  * baked into the graph: they must stay valid until bse_batch_destroy.  `info`
  * holds one int32 per problem and is cleared at the start of every replay.
  * Capture needs a created stream (not the NULL stream). */
@@ -372,9 +370,9 @@ int64_t bse_timing_report(char* buf, int64_t len);
  * call site and for sizes up to size_max, a tile choice:
  *   BSE_TUNE_HEMV_UNIT     size = trailing order m of a Householder step;
  *                          choice = least number of 64 x 64 tiles per block of
- *                          the Hermitian matrix-vector kernel (blocks take equal
- *                          runs of tiles, at most one per compute unit): 1, 2,
- *                          4 or 8
+ *                          the Hermitian matrix-vector kernel of solves that
+ *                          form X+Y (blocks take equal runs of tiles, at most
+ *                          one per compute unit): 1, 2, 4 or 8
  *   BSE_TUNE_GEMM_*        size = problem order n; choice = GEMM tile edge
  *                          16, 32 or 64 (squared form S = U (A+B) U^H; Cholesky
  *                          trailing updates; Householder panel updates; the
@@ -402,13 +400,9 @@ int64_t bse_timing_report(char* buf, int64_t len);
  *                          on 16- and 32-edge tiles: 4 (re = ar br - ai bi,
  *                          im = ar bi + ai br) or 3 (Gauss: ar br, ai bi,
  *                          (ar + ai)(br + bi)); 64-edge tiles always take 4
- *   BSE_TUNE_BATCH_SWEEP   size = largest problem order of a batch; choice =
- *                          blocks of the batched Householder sweep's hemv
- *                          launches: 0 (default) each problem takes the blocks
- *                          it takes on its own (results bitwise equal to the
- *                          single problem path); 1, 2 or 4 that many blocks per
- *                          compute unit in total, shared among the problems in
- *                          proportion to their tiles
+ *   BSE_TUNE_BATCH_SWEEP, BSE_TUNE_BATCH_ALIGN  of an earlier batched
+ *                          reduction: choices 0, 1, 2 or 4 and 0 or 1 are
+ *                          accepted and have no effect
  *   BSE_TUNE_GEMM_VECTORS  size = problem order n; choice = GEMM tile edge
  *                          16, 32 or 64 of the eigenvector path's products:
  *                          the back-transform (W = V^H Z, Z -= V Y), X+Y =
@@ -419,13 +413,6 @@ int64_t bse_timing_report(char* buf, int64_t len);
  *                          (S = U T1, lower triangle); where no entry applies,
  *                          that of BSE_TUNE_GEMM_SQUARED, which then sets the
  *                          first product T1 = (A+B) U^H
- *   BSE_TUNE_BATCH_ALIGN   size = largest problem order of a batch; choice =
- *                          when each problem's batched Householder sweep
- *                          starts: 0 (default) all at the first step; 1 late
- *                          by the largest multiple of the panel width that
- *                          keeps it within the largest problem's steps, so that
- *                          the sweeps end together (every problem's values
- *                          unchanged)
  * Among the entries of a site, the one with the smallest size_max >= size
  * applies; sizes no entry covers use built-in rules.  Every choice gives the
  * same results up to rounding order.  The table is read on the host when work

@@ -1,0 +1,1411 @@
+// Reduction of a Hermitian matrix to real symmetric tridiagonal form in two
+// stages, for the solves that form no eigenvectors (Sec. 4.3 with the probe of
+// Sec. 4.4 carried along): dense to a band of half width BW by block
+// reflectors, whose work is matrix products, then the band to tridiagonal form
+// by chasing bulges down the band.  The one-stage sweep (hetrd.hip) reads the
+// trailing triangle once per column; here it is read and written once per BW
+// columns, in a kernel that is bound by the matrix cores and not by memory.
+//
+// Stage 1, panel k (columns j0 = BW k .., trailing rows and columns t = j0 + BW ..):
+//   k_band_chol   R1 from the Gram matrix of the panel P = S[t:, j0:j0+BW]
+//                 (Cholesky), Q1 = P R1^-1, Gram partials of Q1
+//   k_band_panel  R2 from the Gram matrix of Q1 (the second Cholesky pass makes
+//                 Q = Q1 R2^-1 orthonormal to rounding), then the Householder
+//                 form of Q: Q - [D; 0] = V U' (LU without pivoting, D unit
+//                 modulus against the pivot's phase), H = I - V T V^H with
+//                 T = -U' D^* V_top^-H, and P = H [D R2 R1; 0]
+//   k_band_step   the trailing triangle S -= V W^H + W V^H of the previous
+//                 panel and, from the same registers, the partial products of
+//                 X = S V with this panel's V
+//   k_band_x      X from the partial products, partials of Z = V^H X, H^H on the probe
+//   k_band_w      W = X T - 1/2 V T^H Z T, the next panel's columns updated,
+//                 Gram partials of the next panel
+// Panels whose Gram matrix is not safely positive definite (columns that are
+// dependent, or fewer rows than the factorisation needs) take Householder's
+// column-by-column factorisation in one block of k_band_panel; panels that are
+// zero take H = I.
+//
+// Stage 2: k_band_chase (below).
+//
+// All reductions have a fixed order and no kernel uses floating-point atomics:
+// a repeated run gives the same bits, on its own or in a batch.
+#include <algorithm>
+#include <vector>
+
+#include "bse_internal.h"
+#include "common.h"
+#include "solve_internal.h"
+#include "timing.h"
+
+namespace {
+
+constexpr int BW = BAND_W;
+static_assert(BW == 16, "one 16 x 16 matrix-core tile per block of the band");
+constexpr int RB = 128;           // rows per block of the panel kernels
+constexpr int NT = 512;           // threads of the panel kernels: 8 wavefronts of 16 rows
+constexpr int NWV = NT / 64;
+constexpr int DIRECT_ROWS = 64;   // panels with fewer rows are factored column by column
+constexpr int ST = 64;            // tile edge of k_band_step
+constexpr int LDT = BW + 1;       // padded row of a 16 x 16 tile in LDS
+constexpr int ABS = 2 * BW + 2;   // band storage per column: 2 BW diagonals, the probe, one spare
+                                  // (in LDS a row of the band then steps by 2 BW + 1 values, over
+                                  // all banks; by 2 BW, 16 lanes meet in one)
+
+// Complex elements of the stored band, rounded to 256 bytes.
+__host__ __device__ inline int64_t band_elems(int64_t n) { return (n * ABS + 15) & ~(int64_t)15; }
+
+__host__ __device__ inline int band_ctl_ints(int n) { return 2 + n / CHASE_SWEEPS + 1; }
+
+struct BandProb {
+  double2* M;
+  int64_t ld;
+  int n, ycs;
+  double2* VW;   // n x 64 as four n x BW row-major arrays: V, W of even and of odd panels
+  double2* Q1;   // n x BW row-major
+  double2* X;    // n x BW row-major
+  double2* Y;    // partial products of k_band_step: slots of n x BW
+  double2* g1;   // Gram partials of the panel, BW x BW per block
+  double2* g2;   // Gram partials of Q1
+  double2* z;    // partials of V^H X
+  double2* pd;   // partials of V^H y, BW per block
+  double2* sm;   // T, L1 (BW x BW each)
+  double2* yp;   // probe or null
+  double2* AB;   // band, ABS values per column
+  double *dd, *ee;
+  int32_t* ctl;  // [0] panel state, [1] ticket of the chase, [2 ..] its groups' progress
+  int32_t* info;
+};
+// They travel by value in the kernel arguments, so that the compiler knows every
+// pointer to be device memory (and loads through it do not count as LDS loads).
+struct BandArgs {
+  BandProb p[BAND_BATCH_MAX];
+};
+// A launch's blocks, problem after problem: problem p owns blocks [b[p], b[p+1]);
+// a problem with nothing to do at a step owns none.
+struct BandFirst {
+  int32_t b[BAND_BATCH_MAX + 1];
+};
+
+// The problem that owns this block (a uniform scan of the block ranges in the
+// kernel arguments).
+BSE_DEV int band_problem(const BandFirst& f) {
+  int p = 0;
+  while (p + 1 < BAND_BATCH_MAX && (int)blockIdx.x >= f.b[p + 1]) ++p;
+  return p;
+}
+
+BSE_DEV double2* v_of(const BandProb& p, int k) {
+  return p.VW + (int64_t)(k & 1) * 2 * BW * p.n;
+}
+BSE_DEV double2* w_of(const BandProb& p, int k) {
+  return p.VW + ((int64_t)(k & 1) * 2 + 1) * BW * p.n;
+}
+
+// acc + a b and acc + conj(a) b in four fused operations each
+BSE_DEV double2 cfma(double2 a, double2 b, double2 acc) {
+  return make_double2(fma(-a.y, b.y, fma(a.x, b.x, acc.x)), fma(a.y, b.x, fma(a.x, b.y, acc.y)));
+}
+BSE_DEV double2 cfmac(double2 a, double2 b, double2 acc) {
+  return make_double2(fma(a.y, b.y, fma(a.x, b.x, acc.x)), fma(-a.y, b.x, fma(a.x, b.y, acc.y)));
+}
+BSE_DEV double2 cneg(double2 a) { return make_double2(-a.x, -a.y); }
+BSE_DEV double2 czero() { return make_double2(0.0, 0.0); }
+BSE_DEV double2 keep2(bool ok, double2 v) { return make_double2(ok ? v.x : 0.0, ok ? v.y : 0.0); }
+
+// 1/x and 1/sqrt(x) for positive normal x: the hardware estimate with Newton
+// steps (short dependent chains; both end within an ulp or two).
+BSE_DEV double fast_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+BSE_DEV double fast_rsq(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  const double h = 0.5 * x;
+  r = fma(r, fma(-h * r, r, 0.5), r);
+  return fma(r, fma(-h * r, r, 0.5), r);
+}
+
+template <int CTRL>
+BSE_DEV double dpp_mov(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// Sum over the 16 lanes of each row; every lane of the row gets it.
+BSE_DEV double row_sum(double v) {
+  v += dpp_mov<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp_mov<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_mov<0x141>(v);  // row_half_mirror
+  v += dpp_mov<0x140>(v);  // row_mirror
+  return v;
+}
+BSE_DEV double2 row_sum(double2 v) { return make_double2(row_sum(v.x), row_sum(v.y)); }
+// Sum over the four rows (lanes l, l ^ 16, l ^ 32, l ^ 48); every lane gets it.
+BSE_DEV double quad_rows_sum(double v) {
+  const long long b = __double_as_longlong(v);
+  const auto l0 = __builtin_amdgcn_permlane16_swap((int)b, (int)b, false, false);
+  const auto h0 = __builtin_amdgcn_permlane16_swap((int)(b >> 32), (int)(b >> 32), false, false);
+  v = __longlong_as_double(((long long)h0[0] << 32) | (unsigned int)l0[0]) +
+      __longlong_as_double(((long long)h0[1] << 32) | (unsigned int)l0[1]);
+  const long long c = __double_as_longlong(v);
+  const auto l1 = __builtin_amdgcn_permlane32_swap((int)c, (int)c, false, false);
+  const auto h1 = __builtin_amdgcn_permlane32_swap((int)(c >> 32), (int)(c >> 32), false, false);
+  return __longlong_as_double(((long long)h1[0] << 32) | (unsigned int)l1[0]) +
+         __longlong_as_double(((long long)h1[1] << 32) | (unsigned int)l1[1]);
+}
+BSE_DEV double2 quad_rows_sum(double2 v) {
+  return make_double2(quad_rows_sum(v.x), quad_rows_sum(v.y));
+}
+BSE_DEV double lane_value(double v, int l) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, l);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// One 16 x 16 complex accumulator on the matrix cores, Gauss's three real
+// products per complex one.  Lane l holds of an A operand's chunk c the element
+// (m = l % 16, k = l / 16 + 4 c), of a B operand's (k = l / 16 + 4 c, n = l % 16)
+// and of the result's register r (m = l / 16 + 4 r, n = l % 16): register r of a
+// result is chunk r of the same matrix as a B operand, and of its transpose as
+// an A operand.
+struct Acc {
+  d4 p1 = {0, 0, 0, 0}, p2 = {0, 0, 0, 0}, p3 = {0, 0, 0, 0};
+  BSE_DEV void mac(double2 a, double2 b) {
+    p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, p1, 0, 0, 0);
+    p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, p2, 0, 0, 0);
+    p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x + a.y, b.x + b.y, p3, 0, 0, 0);
+  }
+  BSE_DEV double2 at(int r) const {
+    return make_double2(p1[r] - p2[r], p3[r] - p1[r] - p2[r]);
+  }
+};
+
+BSE_DEV void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Sum of `nb` blocks' 16 x 16 partials into out (256 values, LDS); tmp: 256
+// values.  Two threads per value (even and odd blocks), the order fixed.
+BSE_DEV void sum_partials(const double2* __restrict__ part, int nb, double2* out, double2* tmp) {
+  const int e = threadIdx.x & 255, h = threadIdx.x >> 8;
+  double2 s = czero();
+  int b = h;
+  for (; b + 14 < nb; b += 16) {
+    double2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(b + 2 * u) * 256 + e];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s = cadd(s, v[u]);
+  }
+  for (; b < nb; b += 2) s = cadd(s, part[(int64_t)b * 256 + e]);
+  if (h) tmp[e] = s;
+  __syncthreads();
+  if (!h) out[e] = cadd(s, tmp[e]);
+  __syncthreads();
+}
+
+// Block-wide sum of the wavefronts' 16 x 16 results into part[0..255].
+BSE_DEV void reduce_tiles(const Acc& a, double2* red, double2* __restrict__ part) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    red[wid * 256 + ((lane >> 4) + 4 * r) * BW + (lane & 15)] = a.at(r);
+  __syncthreads();
+  if (threadIdx.x < 256) {
+    double2 s = czero();
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) s = cadd(s, red[w * 256 + threadIdx.x]);
+    part[threadIdx.x] = s;
+  }
+}
+
+struct StepShare {  // values of the current elimination step, two steps' buffers
+  double2 row[2][2][BW];  // pivot row of the matrix and of the augmented identity
+  double2 col[2][BW];     // pivot column
+};
+
+// Cholesky factor and its inverse of the 16 x 16 Hermitian matrix in G (LDS,
+// row-major), by the whole block: threads 0..255 eliminate the matrix, 256..511
+// the identity beside it, one barrier per column.  L and Li: LDS, rows of LDT.
+// Returns false (uniformly) when a pivot is not above tol times its diagonal.
+BSE_DEV bool chol_inv(const double2* G, double2* L, double2* Li, double* dg, StepShare& sh,
+                      double tol) {
+  const int e = threadIdx.x & 255, h = threadIdx.x >> 8, i = e >> 4, j = e & 15;
+  double2 v = h ? make_double2(i == j ? 1.0 : 0.0, 0.0) : G[e];
+  bool ok = true;
+  if (i == 0) sh.row[0][h][j] = v;
+  if (!h && j == 0) sh.col[0][i] = v;
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < BW; ++s) {
+    const int cur = s & 1, nxt = cur ^ 1;
+    const double p = sh.col[cur][s].x;
+    const double2 ci = sh.col[cur][i], rj = sh.row[cur][h][j];
+    ok = ok && p > tol * G[s * BW + s].x;
+    if (i > s && (h || j > s)) v = csub(v, cmul(cscale(ci, fast_rcp(p)), rj));
+    if (s + 1 < BW) {
+      if (i == s + 1) sh.row[nxt][h][j] = v;
+      if (!h && j == s + 1) sh.col[nxt][i] = v;
+      __syncthreads();
+    }
+  }
+  if (!h && i == j) dg[i] = fast_rsq(v.x);
+  __syncthreads();
+  if (!h)
+    L[i * LDT + j] = i >= j ? cscale(v, dg[j]) : czero();
+  else
+    Li[i * LDT + j] = i >= j ? cscale(v, dg[i]) : czero();
+  __syncthreads();
+  return ok;
+}
+
+// ------------------------------------------------------- panel, first pass
+// Q1 = P R1^-1 with R1 from the Gram matrix.  Panel state: 0 ok, 1 the Gram
+// matrix is not safely positive definite, 2 the panel is zero.
+__global__ __launch_bounds__(NT) void k_band_chol(BandArgs a, BandFirst f, int k) {
+  const int pi = band_problem(f);
+  const BandProb& p = a.p[pi];
+  if (failed(p.info)) return;
+  const int bx = (int)blockIdx.x - f.b[pi];
+  const int j0 = BW * k, t = j0 + BW, m = p.n - t, n = p.n;
+  __shared__ double2 red[NWV * 256];
+  __shared__ double2 G[256], tmp[256], L[BW * LDT], Li[BW * LDT];
+  __shared__ double dg[BW];
+  __shared__ StepShare sh;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
+
+  const int row = t + bx * RB + wid * 16 + lo;  // this lane's row of P^T
+  double2 pt[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    pt[c] = p.M[min(row, n - 1) + (int64_t)(j0 + hi + 4 * c) * p.ld];
+  // the partials come from k_band_w over rows j0 .. (t = 0: the first panel)
+  sum_partials(p.g1, cdiv(n - j0, RB), G, tmp);
+  // every column zero: nothing to reflect
+  bool zero = true;
+#pragma unroll
+  for (int s = 0; s < BW; ++s) zero = zero && G[s * BW + s].x == 0.0;
+  if (zero) {
+    if (bx == 0 && tid == 0) p.ctl[0] = 2;
+    return;
+  }
+  // a pivot of 1e-11 of its diagonal leaves the first pass orthonormal to about
+  // 1e-5, which the second pass squares away
+  const bool ok = chol_inv(G, L, Li, dg, sh, 1e-11);
+  if (bx == 0 && tid == 0) p.ctl[0] = ok ? 0 : 1;
+  if (!ok) return;
+  if (bx == 0 && tid < 256) p.sm[256 + tid] = L[(tid >> 4) * LDT + (tid & 15)];
+
+  Acc q;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    q.mac(cconj(Li[lo * LDT + hi + 4 * c]), keep2(row < n, pt[c]));
+  double2* tr = red + wid * 256;  // the wavefront's tile, transposed through LDS
+  double2 qv[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    qv[r] = q.at(r);
+    if (row < n) p.Q1[(int64_t)row * BW + hi + 4 * r] = qv[r];
+    tr[lo * BW + ((hi + 4 * r) ^ lo)] = qv[r];  // [row][vec], swizzled
+  }
+  wave_lds_sync();
+  Acc g;
+  double2 x[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int rr = hi + 4 * c;
+    x[c] = tr[rr * BW + (lo ^ rr)];
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int c = 0; c < 4; ++c) g.mac(cconj(x[c]), x[c]);
+  reduce_tiles(g, red, p.g2 + (int64_t)bx * 256);
+}
+
+// ------------------------------------------------ column-by-column panel
+// Householder factorisation of P = S[t:, j0:j0+BW] by one block, in place
+// (row i <= column j of the result is R), V and T as the fast path leaves them.
+// sums: NWV * BW values, sv: 2 BW values (LDS); Tl: BW * LDT (LDS).
+BSE_DEV void panel_direct(const BandProb& p, int k, double2* sums, double2* sv, double2* Tl) {
+  const int j0 = BW * k, t = j0 + BW, n = p.n, m = n - t;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  double2* V = v_of(p, k);
+  double2* P = p.M + t + (int64_t)j0 * p.ld;
+  auto col = [&](int r, int c) -> double2& { return P[r + (int64_t)c * p.ld]; };
+  // sums over the block of up to BW values per thread, into sv
+  auto block_sums = [&](const double2(&s)[BW]) {
+#pragma unroll
+    for (int c = 0; c < BW; ++c) {
+      const double2 v = wave_sum2(s[c]);
+      if (lane == 0) sums[wid * BW + c] = v;
+    }
+    __syncthreads();
+    if (tid < BW) {
+      double2 v = czero();
+      for (int w = 0; w < NWV; ++w) v = cadd(v, sums[w * BW + tid]);
+      sv[tid] = v;
+    }
+    __syncthreads();
+  };
+  for (int e = tid; e < BW * LDT; e += NT) Tl[e] = czero();
+  for (int64_t e = tid; e < (int64_t)m * BW; e += NT) V[(int64_t)t * BW + e] = czero();
+  __syncthreads();
+  const int jn = min(BW, m);
+  for (int j = 0; j < jn; ++j) {
+    double2 s[BW];
+#pragma unroll
+    for (int c = 0; c < BW; ++c) s[c] = czero();
+    for (int r = j + 1 + tid; r < m; r += NT) {
+      const double2 x = col(r, j);
+#pragma unroll
+      for (int c = 0; c < BW; ++c)
+        if (c >= j) s[c] = cadd(s[c], cmulc(x, col(r, c)));
+    }
+    block_sums(s);
+    const double2 al = col(j, j);
+    const double xn2 = sv[j].x, nn = cabs2(al) + xn2;
+    double2 tau = czero(), scal = czero(), beta = al;
+    if (xn2 != 0.0 && nn > 1e-280) {
+      const double b = -copysign(sqrt(nn), al.x);
+      beta = make_double2(b, 0.0);
+      tau = make_double2((b - al.x) / b, -al.y / b);
+      const double2 dn = make_double2(al.x - b, al.y);
+      const double q = 1.0 / cabs2(dn);
+      scal = make_double2(dn.x * q, -dn.y * q);
+    }
+    // v^H A_c = A[j][c] + conj(scal) s_c
+    double2 gc[BW];
+#pragma unroll
+    for (int c = 0; c < BW; ++c)
+      gc[c] = c > j ? cmulc(tau, cadd(col(j, c), cmulc(scal, sv[c]))) : czero();
+    __syncthreads();  // every thread has read row j
+    for (int r = j + tid; r < m; r += NT) {
+      const double2 v = r == j ? make_double2(1.0, 0.0) : cmul(scal, col(r, j));
+      V[(int64_t)(t + r) * BW + j] = v;
+#pragma unroll
+      for (int c = 0; c < BW; ++c)
+        if (c > j) col(r, c) = csub(col(r, c), cmul(v, gc[c]));
+      if (r == j) col(j, j) = beta;
+    }
+    if (tid == 0) Tl[j * LDT + j] = tau;
+    __syncthreads();
+  }
+  // T[:i, i] = -tau_i T[:i, :i] (V^H v_i)
+  for (int i = 1; i < jn; ++i) {
+    double2 s[BW];
+#pragma unroll
+    for (int c = 0; c < BW; ++c) s[c] = czero();
+    for (int r = i + tid; r < m; r += NT) {
+      const double2 x = V[(int64_t)(t + r) * BW + i];
+#pragma unroll
+      for (int c = 0; c < BW; ++c)
+        if (c < i) s[c] = cadd(s[c], cmulc(V[(int64_t)(t + r) * BW + c], x));
+    }
+    block_sums(s);
+    double2 v = czero();
+    if (tid < i) {
+      for (int c = tid; c < i; ++c) v = cadd(v, cmul(Tl[tid * LDT + c], sv[c]));
+      v = cmul(Tl[i * LDT + i], v);
+    }
+    __syncthreads();
+    if (tid < i) Tl[tid * LDT + i] = make_double2(-v.x, -v.y);
+    __syncthreads();
+  }
+  if (tid < 256) p.sm[tid] = Tl[(tid >> 4) * LDT + (tid & 15)];
+  if (p.yp) {  // V^H y into the first block's partial, the others cleared
+    double2 s[BW];
+#pragma unroll
+    for (int c = 0; c < BW; ++c) s[c] = czero();
+    for (int r = tid; r < m; r += NT) {
+      const double2 y = p.yp[t + r];
+#pragma unroll
+      for (int c = 0; c < BW; ++c) s[c] = cadd(s[c], cmulc(V[(int64_t)(t + r) * BW + c], y));
+    }
+    block_sums(s);
+    const int nb = cdiv(m, RB);
+    for (int e = tid; e < nb * BW; e += NT) p.pd[e] = e < BW ? sv[e] : czero();
+  }
+}
+
+// ------------------------------------------------------ panel, second pass
+__global__ __launch_bounds__(NT) void k_band_panel(BandArgs a, BandFirst f, int k) {
+  const int pi = band_problem(f);
+  const BandProb& p = a.p[pi];
+  if (failed(p.info)) return;
+  const int bx = (int)blockIdx.x - f.b[pi];
+  const int j0 = BW * k, t = j0 + BW, n = p.n, m = n - t;
+  __shared__ double2 red[NWV * 256];
+  __shared__ double2 G[256], tmp[256], L[BW * LDT], Li[BW * LDT];
+  __shared__ double2 U[BW * LDT], Yi[BW * LDT], Dv[BW], ip[BW];
+  __shared__ double dg[BW];
+  __shared__ StepShare sh;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
+  double2* V = v_of(p, k);
+  const int row = t + bx * RB + wid * 16 + lo;
+  int state = m < DIRECT_ROWS ? 1 : p.ctl[0];  // uniform
+  double2 qf[4];
+  if (state == 0) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) qf[c] = p.Q1[(int64_t)min(row, n - 1) * BW + hi + 4 * c];
+    sum_partials(p.g2, cdiv(m, RB), G, tmp);
+    // Q1 has to be near orthonormal for the second pass to end at rounding
+    bool near = true;
+#pragma unroll
+    for (int s = 0; s < BW; ++s) near = near && fabs(G[s * BW + s].x - 1.0) < 0.1;
+    if (!chol_inv(G, L, Li, dg, sh, 0.5) || !near) state = 1;
+  }
+  if (state == 1) {
+    if (bx == 0) panel_direct(p, k, red, G, L);
+    return;
+  }
+  if (state == 2) {  // H = I
+    if (row < n) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) V[(int64_t)row * BW + hi + 4 * r] = czero();
+    }
+    if (tid < BW) p.pd[(int64_t)bx * BW + tid] = czero();
+    if (bx == 0 && tid < 256) p.sm[tid] = czero();
+    return;
+  }
+
+  // ---- Q_top = Q1[:16] R2^-1, then LU of Q_top - D beside the identity
+  const int e = tid & 255, h = tid >> 8, i = e >> 4, j = e & 15;
+  if (!h) tmp[e] = p.Q1[(int64_t)(t + i) * BW + j];
+  __syncthreads();
+  double2 v = make_double2(h && i == j ? 1.0 : 0.0, 0.0);
+  if (!h) {
+#pragma unroll
+    for (int q = 0; q < BW; ++q)  // sum_q Q1[i][q] conj(Li[j][q])
+      v = cadd(v, cmulc(Li[j * LDT + q], tmp[i * BW + q]));
+  }
+  if (i == 0) sh.row[0][h][j] = v;
+  if (!h && j == 0) sh.col[0][i] = v;
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < BW; ++s) {
+    const int cur = s & 1, nxt = cur ^ 1;
+    const double2 pv = sh.col[cur][s];
+    const double2 ci = sh.col[cur][i], rj = sh.row[cur][h][j];
+    const double a2 = cabs2(pv);
+    double2 D = make_double2(-1.0, 0.0), piv = make_double2(1.0, 0.0), inv = piv;
+    if (a2 > 1e-290) {
+      const double ra = fast_rsq(a2), ab = a2 * ra;
+      D = make_double2(-pv.x * ra, -pv.y * ra);
+      piv = csub(pv, D);                               // p (1 + 1/|p|)
+      inv = cscale(cconj(pv), ra * fast_rcp(ab + 1.0));  // 1 / piv
+    }
+    if (i > s) {
+      const double2 li = cmul(ci, inv);
+      if (h || j > s) v = csub(v, cmul(li, rj));
+      if (!h && j == s) v = li;
+    }
+    if (!h && i == s && j == s) {
+      v = piv;
+      Dv[s] = D;
+      ip[s] = inv;
+    }
+    if (s + 1 < BW) {
+      if (i == s + 1) sh.row[nxt][h][j] = v;
+      if (!h && j == s + 1) sh.col[nxt][i] = v;
+      __syncthreads();
+    }
+  }
+  if (!h)
+    U[i * LDT + j] = v;   // U' on and above the diagonal, V_top below it
+  else
+    Yi[i * LDT + j] = v;  // V_top^-1
+  __syncthreads();
+  // ---- X = U'^-1 by backward substitution (threads 0..255, one row per step)
+  double2 x = make_double2(i == j ? 1.0 : 0.0, 0.0);
+  if (!h && i == BW - 1) sh.row[0][0][j] = x = cmul(x, ip[BW - 1]);
+  __syncthreads();
+#pragma unroll
+  for (int s = BW - 1; s > 0; --s) {
+    const int cur = (BW - 1 - s) & 1, nxt = cur ^ 1;
+    if (!h && i < s) {
+      x = csub(x, cmul(U[i * LDT + s], sh.row[cur][0][j]));
+      if (i == s - 1) sh.row[nxt][0][j] = x = cmul(x, ip[s - 1]);
+    }
+    __syncthreads();
+  }
+  if (!h) G[e] = x;
+  __syncthreads();
+  // Mm = R2^-1 U'^-1 (in tmp); T = -U' D^* V_top^-H and R = D R2 R1 by block 0
+  if (!h) {
+    double2 s = czero();
+#pragma unroll
+    for (int q = 0; q < BW; ++q) s = cadd(s, cmulc(Li[q * LDT + i], G[q * BW + j]));
+    tmp[e] = s;
+  } else if (bx == 0) {
+    double2 s = czero(), r = czero();
+#pragma unroll
+    for (int q = 0; q < BW; ++q)
+      if (q >= i) s = csub(s, cmul(cmulc(Dv[q], U[i * LDT + q]), cconj(Yi[j * LDT + q])));
+    p.sm[e] = s;
+    if (i <= j) {
+      for (int q = i; q <= j; ++q)
+        r = cadd(r, cmul(cconj(L[q * LDT + i]), cconj(p.sm[256 + j * BW + q])));
+      p.M[t + i + (int64_t)(j0 + j) * p.ld] = cmul(Dv[i], r);
+    }
+  }
+  __syncthreads();
+  Acc acc;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    acc.mac(tmp[(hi + 4 * c) * BW + lo], keep2(row < n, qf[c]));
+  const bool top = bx == 0 && wid == 0;
+  const double2 y = p.yp ? p.yp[min(row, n - 1)] : czero();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int vec = hi + 4 * r;
+    double2 o = acc.at(r);
+    if (top) o = lo == vec ? make_double2(1.0, 0.0) : keep2(lo > vec, U[lo * LDT + vec]);
+    if (row < n) V[(int64_t)row * BW + vec] = o;
+    const double2 d = row_sum(keep2(row < n, cmulc(o, y)));
+    if (lo == 0) red[wid * BW + vec] = d;
+  }
+  __syncthreads();
+  if (tid < BW) {
+    double2 s = czero();
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) s = cadd(s, red[w * BW + tid]);
+    p.pd[(int64_t)bx * BW + tid] = s;
+  }
+}
+
+// ------------------------------------------------ trailing update and S V
+// Tiles of the lower triangle of the trailing matrix (order m from row t), ST x
+// ST in tile-row order; block b of G takes the run [T b / G, T (b+1) / G).  A
+// tile-row's part inside one run is a piece.  Row r of tile-row Ir collects
+//   Y[p][r]        p = 0 .. nrs - 1   the pieces of tile-row Ir: S V over them
+//   Y[ycs + I][r]  I = Ir .. nI - 1   tile (I, Ir): S_{I,Ir}^H V_I
+__host__ __device__ inline int64_t run_start(int64_t T, int G, int b) { return T * b / G; }
+__host__ __device__ inline int block_of(int64_t T, int G, int64_t t) {
+  return (int)(((t + 1) * G - 1) / T);
+}
+
+constexpr int STEP_THREADS = 256;  // wavefront w: tile columns 16 w .. 16 w + 15
+constexpr int SR = ST / 16;        // 16-row blocks of a tile
+
+struct StepSmem {
+  double2 v[ST][LDT], w[ST][LDT];  // previous panel's V and W, the tile-row's rows
+  double2 x[ST][LDT];              // this panel's V
+  double2 tr[4][16 * LDT];         // per wavefront: a 16 x 16 block, transposed
+};
+
+__global__ __launch_bounds__(STEP_THREADS) void k_band_step(BandArgs a, BandFirst f, int k) {
+  const int pi = band_problem(f);
+  const BandProb& p = a.p[pi];
+  if (failed(p.info)) return;
+  const int bx = (int)blockIdx.x - f.b[pi], G = f.b[pi + 1] - f.b[pi];
+  const int t = BW * (k + 1), n = p.n, nI = cdiv(n - t, ST);
+  const int64_t T = (int64_t)nI * (nI + 1) / 2, N16 = (int64_t)n * BW, ld = p.ld;
+  const int64_t t_end = run_start(T, G, bx + 1);
+  __shared__ StepSmem sm;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
+  const bool upd = k > 0;  // a previous panel to apply
+  const double2* __restrict__ Vn = v_of(p, k);
+  const double2* __restrict__ Vp = v_of(p, k - 1);
+  const double2* __restrict__ Wp = w_of(p, k - 1);
+  double2* __restrict__ M = p.M;
+  double2* __restrict__ Y = p.Y;
+
+  int64_t tt = run_start(T, G, bx);
+  int I = (int)((sqrt(8.0 * (double)tt + 1.0) - 1.0) * 0.5);
+  if ((int64_t)(I + 1) * (I + 2) / 2 <= tt) ++I;
+  if ((int64_t)I * (I + 1) / 2 > tt) --I;
+  int J = (int)(tt - (int64_t)I * (I + 1) / 2);
+
+  auto stage_rows = [&]() {  // the tile-row's rows of V, W and this panel's V
+    for (int e = tid; e < ST * BW; e += STEP_THREADS) {
+      const int r = e >> 4, c = e & 15, row = t + I * ST + r;
+      const int64_t at = (int64_t)min(row, n - 1) * BW + c;
+      const bool ok = row < n;
+      sm.x[r][c] = keep2(ok, Vn[at]);
+      if (upd) {
+        sm.v[r][c] = keep2(ok, Vp[at]);
+        sm.w[r][c] = keep2(ok, Wp[at]);
+      }
+    }
+  };
+  // block (rs, wid) of tile (I, J), as the transposed 16 x 16 block: register r
+  // of lane l holds row l % 16, column l / 16 + 4 r
+  auto load = [&](double2(&s)[4], int I_, int J_, int rs) {
+    const int64_t row = min(t + I_ * ST + rs * 16 + lo, n - 1);
+    const int c0 = t + J_ * ST + wid * 16 + hi;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s[r] = M[row + (int64_t)min(c0 + 4 * r, n - 1) * ld];
+  };
+
+  Acc row_acc[SR];
+  stage_rows();
+  double2 s[4], sn[4];
+  load(s, I, J, 0);
+  __syncthreads();
+  while (tt < t_end) {  // uniform
+    const int cj = t + J * ST + wid * 16;  // first column of this wavefront
+    // this wavefront's columns of the operands
+    double2 aw[4], av[4], ax[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const bool okm = cj + lo < n, okk = cj + hi + 4 * c < n;
+      const int64_t at = (int64_t)min(cj + lo, n - 1) * BW + hi + 4 * c;
+      if (upd) {
+        aw[c] = keep2(okm, cconj(Wp[at]));
+        av[c] = keep2(okm, cconj(Vp[at]));
+      }
+      ax[c] = keep2(okk, Vn[(int64_t)min(cj + hi + 4 * c, n - 1) * BW + lo]);
+    }
+    const int In = J + 1 > I ? I + 1 : I, Jn = J + 1 > I ? 0 : J + 1;
+    const bool more = tt + 1 < t_end;
+    Acc col;
+#pragma unroll
+    for (int rs = 0; rs < SR; ++rs) {
+      // the next block's loads (past the run: this tile again, unused)
+      if (rs + 1 < SR)
+        load(sn, I, J, rs + 1);
+      else
+        load(sn, more ? In : I, more ? Jn : J, 0);
+      const bool below = I != J || rs > wid, diag = I == J && rs == wid;  // uniform
+      if (below || diag) {
+        const int r0 = rs * 16;
+        if (upd) {
+          Acc u;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) u.mac(aw[c], sm.v[r0 + lo][hi + 4 * c]);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) u.mac(av[c], sm.w[r0 + lo][hi + 4 * c]);
+          const int row = t + I * ST + r0 + lo;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            s[r] = csub(s[r], u.at(r));
+            const int colr = cj + hi + 4 * r;
+            if (row < n && colr < n && (below || lo >= hi + 4 * r))
+              M[row + (int64_t)colr * ld] = s[r];
+          }
+        }
+        if (diag) {  // lower triangle of the block, the diagonal real
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int cc = hi + 4 * r;
+            s[r] = make_double2(lo >= cc ? s[r].x : 0.0, lo > cc ? s[r].y : 0.0);
+          }
+        }
+        // transposed through LDS for the product with S^H
+        double2* tr = sm.tr[wid];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tr[(hi + 4 * r) * LDT + lo] = s[r];
+        wave_lds_sync();
+#pragma unroll
+        for (int c = 0; c < 4; ++c) row_acc[rs].mac(ax[c], s[c]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          double2 v = cconj(tr[lo * LDT + hi + 4 * c]);  // conj S[row hi + 4c][column lo]
+          if (diag && lo == hi + 4 * c) v = czero();
+          col.mac(sm.x[r0 + hi + 4 * c][lo], v);
+        }
+        wave_lds_sync();
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s[r] = sn[r];
+    }
+    // S_IJ^H V_I: [vec][column] of this wavefront's 16 columns
+    if (cj + lo < n) {
+      double2* y = Y + (int64_t)(p.ycs + I) * N16 + (int64_t)(cj + lo) * BW;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) y[hi + 4 * r] = col.at(r);
+    }
+    if (J == I || !more) {
+      // end of a piece: the wavefronts' row sums, two 16-row blocks at a time
+      // through the operand rows' space
+      double2* red = &sm.v[0][0];  // 4 x 2 x 256 values of the 3 ST LDT there are
+      static_assert(4 * 2 * 256 <= 3 * ST * LDT, "row sums fit in the operand rows");
+      const int slot = bx - block_of(T, G, (int64_t)I * (I + 1) / 2);
+      double2* y = Y + (int64_t)slot * N16;
+#pragma unroll
+      for (int half = 0; half < SR / 2; ++half) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            red[(wid * 2 + q) * 256 + lo * BW + hi + 4 * r] = row_acc[2 * half + q].at(r);
+        __syncthreads();
+        for (int e = tid; e < 2 * 256; e += STEP_THREADS) {
+          const int row = t + I * ST + half * 32 + (e >> 4);
+          double2 o = czero();
+#pragma unroll
+          for (int w = 0; w < 4; ++w) o = cadd(o, red[w * 512 + e]);
+          if (row < n) y[(int64_t)row * BW + (e & 15)] = o;
+        }
+      }
+#pragma unroll
+      for (int rs = 0; rs < SR; ++rs) row_acc[rs] = Acc();
+      __syncthreads();
+      if (more) {
+        I = In;
+        J = Jn;
+        stage_rows();
+        __syncthreads();
+      }
+    } else {
+      J = Jn;
+    }
+    ++tt;
+  }
+}
+
+// --------------------------------------------------- X, V^H X and the probe
+__global__ __launch_bounds__(NT) void k_band_x(BandArgs a, BandFirst f, int k, BandFirst gs) {
+  const int pi = band_problem(f);
+  const BandProb& p = a.p[pi];
+  if (failed(p.info)) return;
+  const int bx = (int)blockIdx.x - f.b[pi];
+  const int t = BW * (k + 1), n = p.n, m = n - t, nI = cdiv(m, ST);
+  const int G = gs.b[pi];  // blocks of this problem's k_band_step launch
+  const int64_t T = (int64_t)nI * (nI + 1) / 2, N16 = (int64_t)n * BW;
+  __shared__ double2 xs[RB * LDT];
+  __shared__ double2 red[NWV * 256];
+  __shared__ double2 sc[BW];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
+  const double2* V = v_of(p, k);
+  // the sums over the slots, four values per thread
+#pragma unroll
+  for (int q = 0; q < RB * BW / NT; ++q) {
+    const int e = tid + q * NT, rr = e >> 4, c = e & 15, lr = bx * RB + rr;
+    double2 x = czero();
+    if (lr < m) {
+      const int Ir = lr / ST;
+      const int64_t s0 = (int64_t)Ir * (Ir + 1) / 2;
+      const int nrs = block_of(T, G, s0 + Ir) - block_of(T, G, s0) + 1;
+      const int tot = nrs + nI - Ir;
+      const double2* y = p.Y + (int64_t)(t + lr) * BW + c;
+      auto at = [&](int u) { return y + (int64_t)(u < nrs ? u : p.ycs + Ir + u - nrs) * N16; };
+      int u = 0;
+      for (; u + 8 <= tot; u += 8) {
+        double2 v[8];
+#pragma unroll
+        for (int w = 0; w < 8; ++w) v[w] = *at(u + w);
+#pragma unroll
+        for (int w = 0; w < 8; ++w) x = cadd(x, v[w]);
+      }
+      for (; u < tot; ++u) x = cadd(x, *at(u));
+      p.X[(int64_t)(t + lr) * BW + c] = x;
+    }
+    xs[rr * LDT + c] = x;
+  }
+  if (p.yp) {  // sum of the blocks' V^H y
+    const int c = tid & 15, g = tid >> 4;  // 32 groups
+    double2 s = czero();
+    for (int b = g; b < cdiv(m, RB); b += NT / BW) s = cadd(s, p.pd[(int64_t)b * BW + c]);
+    red[g * BW + c] = s;
+  }
+  __syncthreads();
+  if (p.yp && tid < BW) {
+    double2 s = czero();
+    for (int g = 0; g < NT / BW; ++g) s = cadd(s, red[g * BW + tid]);
+    sc[tid] = s;
+  }
+  Acc z;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int rr = wid * 16 + hi + 4 * c, row = t + bx * RB + rr;
+    z.mac(keep2(row < n, cconj(V[(int64_t)min(row, n - 1) * BW + lo])), xs[rr * LDT + lo]);
+  }
+  __syncthreads();
+  reduce_tiles(z, red, p.z + (int64_t)bx * 256);
+  if (p.yp && tid < RB && bx * RB + tid < m) {
+    // y -= V (T^H (V^H y))
+    const int row = t + bx * RB + tid;
+    double2 d = czero();
+    for (int j = 0; j < BW; ++j) {
+      double2 cj = czero();
+      for (int i = 0; i <= j; ++i) cj = cadd(cj, cmulc(p.sm[i * BW + j], sc[i]));
+      d = cadd(d, cmul(V[(int64_t)row * BW + j], cj));
+    }
+    p.yp[row] = csub(p.yp[row], d);
+  }
+}
+
+// ------------------------------------- W, the next panel's columns, its Gram
+// k < 0: nothing to apply, the Gram partials of the first panel.
+__global__ __launch_bounds__(NT) void k_band_w(BandArgs a, BandFirst f, int k) {
+  const int pi = band_problem(f);
+  const BandProb& p = a.p[pi];
+  if (failed(p.info)) return;
+  const int bx = (int)blockIdx.x - f.b[pi];
+  const int t = BW * (k + 1), n = p.n, m = n - t;
+  __shared__ double2 red[NWV * 256];
+  __shared__ double2 Z[256], tmp[256], Ts[256];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
+  const int row = t + bx * RB + wid * 16 + lo;
+  double2 s[4];  // the next panel's columns t .. t + 15 on this row (transposed block)
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    s[r] = p.M[min(row, n - 1) + (int64_t)min(t + hi + 4 * r, n - 1) * p.ld];
+  if (k >= 0) {
+    const double2* V = v_of(p, k);
+    double2* W = w_of(p, k);
+    double2 xf[4], vf[4], xc[4], vc[4];  // rows of X and V: this tile's, the top tile's
+    const int rt = min(t + lo, n - 1);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int64_t at = (int64_t)min(row, n - 1) * BW + hi + 4 * c, ac = (int64_t)rt * BW + hi + 4 * c;
+      xf[c] = keep2(row < n, p.X[at]);
+      vf[c] = keep2(row < n, V[at]);
+      xc[c] = keep2(t + lo < n, p.X[ac]);
+      vc[c] = keep2(t + lo < n, V[ac]);
+    }
+    if (tid < 256) Ts[tid] = p.sm[tid];
+    sum_partials(p.z, cdiv(m, RB), Z, tmp);
+    Acc zt, nn;  // Z T, T^H (Z T)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) zt.mac(Z[lo * BW + hi + 4 * c], Ts[(hi + 4 * c) * BW + lo]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) nn.mac(cconj(Ts[(hi + 4 * c) * BW + lo]), zt.at(c));
+    double2 nh[4], tt[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      nh[c] = cscale(nn.at(c), -0.5);  // A operand of -1/2 (T^H Z T)^T
+      tt[c] = Ts[(hi + 4 * c) * BW + lo];  // A operand of T^T
+    }
+    Acc wt, wc;  // W^T of this tile and of the top tile
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      wt.mac(tt[c], xf[c]);
+      wc.mac(tt[c], xc[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      wt.mac(nh[c], vf[c]);
+      wc.mac(nh[c], vc[c]);
+    }
+    Acc u;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double2 wr = wt.at(r);
+      if (row < n) W[(int64_t)row * BW + hi + 4 * r] = wr;
+      u.mac(cconj(wc.at(r)), vf[r]);
+      u.mac(cconj(vc[r]), wr);
+    }
+    // lower triangle only in the top tile, its diagonal real
+    const bool top = bx == 0 && wid == 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = hi + 4 * r;
+      s[r] = csub(s[r], u.at(r));
+      if (top && lo == c) s[r].y = 0.0;
+      if (row < n && t + c < n && (!top || lo >= c)) p.M[row + (int64_t)(t + c) * p.ld] = s[r];
+    }
+  }
+  // Gram partials of the next panel: rows t + 16 ..
+  Acc g;
+  {
+    double2* tr = red + wid * 256;
+    const bool ok = row < n && row >= t + BW;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = hi + 4 * r;
+      tr[lo * BW + (c ^ lo)] = keep2(ok && t + c < n, s[r]);
+    }
+    wave_lds_sync();
+    double2 x[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int rr = hi + 4 * c;
+      x[c] = tr[rr * BW + (lo ^ rr)];
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) g.mac(cconj(x[c]), x[c]);
+  }
+  reduce_tiles(g, red, p.g1 + (int64_t)bx * 256);
+}
+
+// ------------------------------------------------------------ band storage
+// AB[c][d] = S[c + d][c] for d <= BW, zero for the diagonals that bulges will
+// use, and the probe; the
+// chase's ticket and progress words are cleared.
+__global__ void k_band_pack(BandArgs a, BandFirst f) {
+  const int pi = band_problem(f);
+  const BandProb& p = a.p[pi];
+  if (failed(p.info)) return;
+  const int bx = (int)blockIdx.x - f.b[pi], nb = f.b[pi + 1] - f.b[pi];
+  const int n = p.n;
+  for (int64_t e = (int64_t)bx * blockDim.x + threadIdx.x; e < (int64_t)n * ABS;
+       e += (int64_t)nb * blockDim.x) {
+    const int c = (int)(e / ABS), d = (int)(e % ABS);
+    double2 v = czero();
+    if (d <= BW && c + d < n) v = p.M[c + d + (int64_t)c * p.ld];
+    if (d == 0) v.y = 0.0;
+    if (d == 2 * BW && p.yp) v = p.yp[c];
+    p.AB[e] = v;
+  }
+  for (int e = bx * blockDim.x + threadIdx.x; e < band_ctl_ints(n); e += nb * blockDim.x)
+    p.ctl[e] = 0;
+}
+
+// -------------------------------------------------------------- the chase
+// Band to tridiagonal.  Sweep s (s = 0 .. n - 2) reduces column s: its task k =
+// 0 forms the reflector of A[s+1 .. s+BW, s] and applies it on both sides of
+// the diagonal block; task k >= 1, on rows R_k = s + 1 + BW k .. (BW of them) and
+// columns R_{k-1}, applies the previous reflector from the right to that block,
+// forms the reflector that annihilates the block's first column below its first
+// row, and applies it from the left to the block and on both sides to the
+// diagonal block of R_k.  Only the first column of a bulge is annihilated; the
+// rest stays for the next sweep, whose blocks sit one row further down, so 2 BW
+// diagonals are stored.  Task (s, k) needs task (s - 1, k + 1) to be done: sweep s
+// runs two tasks behind sweep s - 1.
+//
+// A block takes CS consecutive sweeps (a group) and moves with them down the
+// band: at step i sweep w of the group does task i - 2 w, with one barrier per
+// step; the columns in use lie in a ring of LDS.  A column leaves the ring for
+// memory when the group's last sweep has passed it, and the next group's first
+// sweep takes it from there.  The chain of dependent tasks, 2 n of them, is what
+// bounds the kernel: grouping keeps the hand-over between blocks out of all but
+// one step in 2 CS, and wavefronts of their own carry the columns into the ring
+// (FW of them, requests two steps ahead) and out of it (LW of them), so that the
+// sweeps do not wait for memory.
+//
+// Groups are taken in order from a ticket counter, and a group waits only for
+// progress of the group before it, which a running block holds, so every wait
+// ends whatever blocks are resident.  Columns that pass between blocks are
+// stored through the L2 caches and loaded past them (device scope, the XCDs' L2
+// caches are not coherent by themselves); the progress word follows a wait for
+// the stores.
+constexpr int CS = CHASE_SWEEPS;
+constexpr int FW = 2;  // wavefronts that fetch columns, in turn
+constexpr int LW = 2;  // wavefronts that store finished columns, in turn
+constexpr int CH_THREADS = 64 * (2 * CS + FW + LW);
+constexpr int RING = 256;  // columns in LDS: 31 CS + 17 in use, 16 more on their way out
+static_assert(31 * CS + 17 + 16 <= RING, "the ring holds a group's columns");
+constexpr int CHASE_SPIN = 1 << 22;  // polls before a group gives up (never reached in order)
+
+// 16-byte loads and stores at device scope (sc1).  The buffer descriptor's size
+// makes loads past the band zero and drops stores there.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+constexpr int DEVICE_SCOPE = 0x10;
+constexpr int BUFFER_FLAGS = 0x00027000;  // raw buffer, 32-bit data
+
+// One task of a sweep takes two wavefronts: one works on the block below the
+// diagonal and forms the reflector, the other applies the reflector to the
+// diagonal block and the probe one step later (what the next sweep needs of them
+// is then still one step ahead of its use).  The kernel is bound by the
+// instructions its four SIMDs issue per step, so the products with vectors run
+// on the vector ALU (four values per lane, then sums over the lane groups) and
+// the rank-two updates on the matrix cores, which take the vectors at index
+// lo = l % 16 as they are: a 16 x 16 x 4 product holds both complex outer products
+// of an update, one for its real and one for its imaginary part.  Blocks that are
+// updated are held as the matrix cores return them: register r of lane l the
+// element at row hi + 4 r, hi = l / 16, and column lo.
+BSE_DEV double pick4(int hi, double a, double b, double c, double d) {
+  return hi < 2 ? (hi == 0 ? a : b) : (hi == 2 ? c : d);
+}
+
+// The block at rows r0 .. r0 + 15 and columns r0 - 16 .. r0 - 1 (first: the column
+// s alone), by one wavefront: the previous reflector from the right, B - z v^H; the
+// reflector u of the first column x; and u from the left,
+//   B - z v^H - u G,  G = conj(tau) (u^H B - (u^H z) v^H),
+// u^H z from the first column of u^H B and u^H x = x_0 + conj(scal) sum_{i>0} |x_i|^2.
+// x: the first column (element lo); v, vq, tau: the sweep's reflector at lo and at
+// hi + 4 c (in: of the previous task; out: u).  ub: BW + 1 values of LDS that take u
+// and tau for the other wavefront.  Returns the column's new first element.
+BSE_DEV double chase_bulge(double2* ring, double2* ub, int lo, int hi, int r0, bool first,
+                           double2 x, double2& v, double2 (&vq)[4], double2& tau) {
+  // element (i, j) of the block is diagonal BW + i - j of column r0 - BW + j
+  auto at = [&](int i, int j) { return ((r0 - BW + j) & (RING - 1)) * ABS + BW + i - j; };
+  double2 Bt[4], xq[4], z = czero(), b0 = czero();
+  if (!first) {  // uniform
+    double2 z0 = czero(), z1 = czero(), B[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) B[c] = ring[at(lo, hi + 4 * c)];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) Bt[c] = ring[at(hi + 4 * c, lo)];
+    b0 = ring[at(0, lo)];
+    z0 = cfma(B[0], vq[0], z0);
+    z1 = cfma(B[1], vq[1], z1);
+    z0 = cfma(B[2], vq[2], z0);
+    z1 = cfma(B[3], vq[3], z1);
+    z = cmul(tau, quad_rows_sum(cadd(z0, z1)));
+    x = csub(x, z);  // the reflector's first element is 1
+  }
+  ub[lo] = x;  // (the four lane groups hold the same values)
+  wave_lds_sync();
+#pragma unroll
+  for (int c = 0; c < 4; ++c) xq[c] = ub[hi + 4 * c];
+  // beta, tau, scal: I - tau u u^H with u = (1, scal x_1, ...) takes x to (beta, 0, ...)
+  const double xn2 = row_sum(lo > 0 ? cabs2(x) : 0.0);
+  const double2 al = make_double2(lane_value(x.x, 0), lane_value(x.y, 0));
+  const double nn = fma(al.x, al.x, fma(al.y, al.y, xn2));
+  const bool ok = nn > 1e-280 && (xn2 != 0.0 || al.y != 0.0);
+  const double r = fast_rsq(nn), rb = -copysign(r, al.x), b = nn * rb;
+  const double2 dn = make_double2(al.x - b, al.y);
+  const double q = fast_rcp(cabs2(dn));
+  const double2 scal = keep2(ok, make_double2(dn.x * q, -dn.y * q));
+  const double2 tn = keep2(ok, make_double2(-dn.x * rb, -al.y * rb));
+  const double beta = ok ? b : al.x;
+  double2 u = cmul(scal, x);
+  u.x = lo == 0 ? 1.0 : u.x;
+  u.y = lo == 0 ? 0.0 : u.y;
+  if (!first) {
+    // u^H B with the unscaled x (it does not wait for the scalars)
+    double2 g0 = czero(), g1 = czero();
+    g0 = cfmac(keep2(hi > 0, xq[0]), Bt[0], g0);
+    g1 = cfmac(xq[1], Bt[1], g1);
+    g0 = cfmac(xq[2], Bt[2], g0);
+    g1 = cfmac(xq[3], Bt[3], g1);
+    const double2 ug = cfmac(scal, quad_rows_sum(cadd(g0, g1)), b0);
+    const double2 ux = make_double2(fma(scal.x, xn2, al.x), fma(-scal.y, xn2, al.y));
+    const double2 uz = csub(make_double2(lane_value(ug.x, 0), lane_value(ug.y, 0)), ux);
+    const double2 G = cmulc(tn, cfmac(v, cneg(uz), ug));
+    const double ma = pick4(hi, z.x, z.y, u.x, u.y);
+    const double mr = pick4(hi, -v.x, -v.y, -G.x, G.y);
+    const double mi = pick4(hi, v.y, -v.x, -G.y, -G.x);
+    d4 re, im;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      re[c] = Bt[c].x;
+      im[c] = Bt[c].y;
+    }
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(ma, mr, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(ma, mi, im, 0, 0, 0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      // the first column is known: (beta, 0, ...)
+      double2 o = make_double2(re[c], im[c]);
+      o.x = lo ? o.x : (c == 0 && hi == 0 ? beta : 0.0);
+      o.y = lo ? o.y : 0.0;
+      ring[at(hi + 4 * c, lo)] = o;
+    }
+  }
+  ub[lo] = u;
+  ub[BW] = tn;
+  tau = tn;
+  v = u;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) vq[c] = cmul(scal, xq[c]);
+  vq[0].x = hi == 0 ? 1.0 : vq[0].x;
+  vq[0].y = hi == 0 ? 0.0 : vq[0].y;
+  return beta;
+}
+
+// The diagonal block at rows r0 .. r0 + 15 and the probe's rows, with the reflector
+// in ub: D := H^H D H = D - u w^H - w u^H, w = tau D u - 1/2 |tau|^2 (u^H D u) u, and
+// y := H^H y.
+BSE_DEV void chase_diag(double2* ring, const double2* ub, int lo, int hi, int r0) {
+  auto slot = [&](int c) { return ((r0 + c) & (RING - 1)) * ABS; };
+  int oD[4];
+  double2 D[4], uq[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int i = hi + 4 * c;
+    oD[c] = slot(min(i, lo)) + abs(i - lo);
+    D[c] = ring[oD[c]];
+    uq[c] = ub[i];
+  }
+  const int oy = slot(lo) + 2 * BW;
+  const double2 u = ub[lo], tau = ub[BW], y = ring[oy];
+  double2 q0 = czero(), q1 = czero();  // (D u)_lo = sum_i conj(D_i,lo) u_i
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int i = hi + 4 * c;
+    D[c].y = i == lo ? 0.0 : i > lo ? D[c].y : -D[c].y;
+    if (c & 1)
+      q1 = cfmac(D[c], uq[c], q1);
+    else
+      q0 = cfmac(D[c], uq[c], q0);
+  }
+  const double2 sy = row_sum(cmulc(u, y));
+  const double2 q = quad_rows_sum(cadd(q0, q1));
+  const double uq2 = row_sum(fma(u.x, q.x, u.y * q.y));
+  const double hl = -0.5 * cabs2(tau) * uq2;
+  const double2 tq = cmul(tau, q);
+  const double2 w = make_double2(fma(u.x, hl, tq.x), fma(u.y, hl, tq.y));
+  const double ma = pick4(hi, u.x, u.y, w.x, w.y);
+  const double mr = pick4(hi, -w.x, -w.y, -u.x, -u.y);
+  const double mi = pick4(hi, w.y, -w.x, u.y, -u.x);
+  d4 re, im;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    re[c] = D[c].x;
+    im[c] = D[c].y;
+  }
+  re = __builtin_amdgcn_mfma_f64_16x16x4f64(ma, mr, re, 0, 0, 0);
+  im = __builtin_amdgcn_mfma_f64_16x16x4f64(ma, mi, im, 0, 0, 0);
+  if (hi == 0) ring[oy] = cfma(cmulc(tau, u), cneg(sy), y);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int i = hi + 4 * c;
+    if (i >= lo) ring[oD[c]] = make_double2(re[c], i == lo ? 0.0 : im[c]);
+  }
+}
+
+// The lane number, opaque to the compiler: what a kind of wavefront derives from
+// it stays inside that kind's loop (hoisted out of it, the index values of all
+// kinds would be live, and spilled, in each).
+BSE_DEV int opaque_lane() {
+  int l = threadIdx.x & 63;
+  asm volatile("" : "+v"(l));
+  return l;
+}
+
+__global__ __launch_bounds__(CH_THREADS) void k_band_chase(BandArgs a, int np, int gmax) {
+  __shared__ double2 ring[RING * ABS];
+  __shared__ double2 ub[CS][2][BW + 1];
+  __shared__ int tick;
+  constexpr int CHUNK = BW * ABS;  // values of 16 columns
+  constexpr int PER = (CHUNK + 63) / 64;
+  const int tid = threadIdx.x;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto slot = [](int c) { return (c & (RING - 1)) * ABS; };
+  auto wrap = [](int e) { return e >= RING * ABS ? e - RING * ABS : e; };
+  for (;;) {
+    __syncthreads();
+    if (tid == 0)
+      tick = __hip_atomic_fetch_add(a.p[0].ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int tk = __builtin_amdgcn_readfirstlane(tick);
+    const int pi = tk % np, g = tk / np;
+    if (g >= gmax) return;  // every ticket is taken
+    const BandProb& p = a.p[pi];
+    const int n = p.n, s0 = g * CS;
+    if (s0 >= max(n - 1, 1) || failed(p.info)) continue;
+    const __amdgpu_buffer_rsrc_t AB = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)p.AB, (short)0, n * ABS * (int)sizeof(double2), BUFFER_FLAGS);
+    int32_t* prog = p.ctl + 2;
+    int seen = g ? 0 : n;  // columns below this are final in memory
+    // wait until the previous group has left every column below `need`
+    auto wait_for = [&](int need) {
+      for (int spin = 0; seen < need; ++spin) {
+        seen = __hip_atomic_load(prog + g - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (spin > CHASE_SPIN) {
+          set_info(p.info, BSE_INFO_NO_CONVERGE);
+          seen = n;
+        }
+      }
+      asm volatile("" ::: "memory");
+    };
+    // columns c0 .. c0 + 15 by one wavefront; columns past the band come as zeros,
+    // which the last tasks' blocks reach
+    u32x4 pre[PER];
+    auto fetch = [&](int lane, int c0) {
+#pragma unroll
+      for (int u = 0; u < PER; ++u)
+        pre[u] = __builtin_amdgcn_raw_buffer_load_b128(AB, (c0 * ABS + lane + 64 * u) * 16, 0,
+                                                       DEVICE_SCOPE);
+    };
+    auto put = [&](int lane, int c0) {
+      const int to = (c0 & (RING - 1)) * ABS + lane;
+#pragma unroll
+      for (int u = 0; u < PER; ++u)
+        if (lane + 64 * u < CHUNK) *(u32x4*)&ring[wrap(to + 64 * u)] = pre[u];
+    };
+    const int slast = min(s0 + CS, n - 1) - 1;  // last sweep of the group
+    // its last task, the diagonal block one step later
+    const int steps = n > 1 ? 2 * (slast - s0) + (n - 2 - slast) / BW + 2 : 0;
+    const int dw = wid - CS, fw = wid - 2 * CS;  // diagonal; fetching (FW: storing)
+    const int lw = fw - FW;
+    // step j takes columns s0 + 16 j + 1 .. + 16; s0 and those of step 0 first
+    if (fw == 0 || fw == 1) {
+      const int lane = opaque_lane();
+      wait_for(min(n, s0 + BW + 1));
+      fetch(lane, s0 + fw);
+      put(lane, s0 + fw);
+      if (fw == 1) {  // for step 1, put at step 0
+        wait_for(min(n, s0 + 2 * BW + 1));
+        fetch(lane, s0 + BW + 1);
+      }
+    }
+    __syncthreads();
+    // the three kinds of wavefronts, each with one barrier per step
+    if (dw < 0) {
+      const int lane = opaque_lane(), lo = lane & 15, hi = lane >> 4;
+      double2 vq[4] = {}, v = czero(), tau = czero();
+      const int s = s0 + wid;
+      for (int i = 0; i < steps; ++i) {
+        const int k = i - 2 * wid, r0 = s + 1 + BW * k;  // first row of the task
+        if (s <= slast && k >= 0 && r0 < n) {            // uniform
+          const double2 x = ring[k ? slot(r0 - BW) + BW + lo : slot(s) + 1 + lo];
+          const double beta = chase_bulge(ring, ub[wid][i & 1], lo, hi, r0, k == 0, x, v, vq, tau);
+          if (k == 0 && lane == 0) {
+            p.ee[s] = beta;
+            p.dd[s] = ring[slot(s)].x;
+            if (p.yp) p.yp[s] = ring[slot(s) + 2 * BW];
+          }
+        }
+        __syncthreads();
+      }
+    } else if (fw < 0) {
+      const int lane = opaque_lane(), lo = lane & 15, hi = lane >> 4;
+      const int s = s0 + dw;
+      for (int i = 0; i < steps; ++i) {
+        const int k = i - 1 - 2 * dw, r0 = s + 1 + BW * k;
+        if (s <= slast && k >= 0 && r0 < n)  // uniform
+          chase_diag(ring, ub[dw][(i & 1) ^ 1], lo, hi, r0);
+        __syncthreads();
+      }
+    } else if (lw < 0) {
+      const int lane = opaque_lane();
+      for (int i = 0; i < steps; ++i) {
+        if ((i & 1) == fw) {  // request the columns of step i + 2
+          wait_for(min(n, s0 + BW * (i + 3) + 1));
+          fetch(lane, s0 + BW * (i + 2) + 1);
+        } else {
+          put(lane, s0 + BW * (i + 1) + 1);
+        }
+        __syncthreads();
+      }
+    } else {
+      // columns that the group's last sweep passed at step i - 1 go to memory at
+      // step i and are published at step i + 1
+      const int lane = opaque_lane();
+      int left = 0;
+      for (int i = 0; i < steps; ++i) {
+        const int kl = i - 1 - 2 * (CS - 1);
+        if ((i & (LW - 1)) == lw) {
+          if (kl >= 1) {
+            const int c0 = s0 + CS + BW * (kl - 1);
+            const int from = (c0 & (RING - 1)) * ABS + lane;
+            u32x4 v[PER];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) v[u] = *(const u32x4*)&ring[wrap(from + 64 * u)];
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+              if (lane + 64 * u < CHUNK)
+                __builtin_amdgcn_raw_buffer_store_b128(v[u], AB, (c0 * ABS + lane + 64 * u) * 16, 0,
+                                                       DEVICE_SCOPE);
+            left = min(c0 + BW, n);
+          }
+        } else if (left) {
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          if (lane == 0)
+            __hip_atomic_store(prog + g, left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+      }
+    }
+    // what is left of the band, and the last diagonal element
+    {
+      const int kl = steps - 2 - 2 * (CS - 1);
+      const int c0 = s0 + CS + (kl >= 1 ? BW * kl : 0);
+      const int from = (c0 & (RING - 1)) * ABS;
+      for (int e = tid; e < (n - c0) * ABS; e += CH_THREADS)
+        __builtin_amdgcn_raw_buffer_store_b128(*(const u32x4*)&ring[wrap(from + e)], AB,
+                                               (c0 * ABS + e) * 16, 0, DEVICE_SCOPE);
+    }
+    if (slast == n - 2 && tid == 0) {
+      const int last = n - 1;
+      p.dd[last] = ring[slot(last)].x;
+      if (p.yp) p.yp[last] = ring[slot(last) + 2 * BW];
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) __hip_atomic_store(prog + g, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+int device_cus() {
+  static const int cus = [] {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
+      v = 256;
+    return v;
+  }();
+  return cus;
+}
+
+// The control words in complex elements, rounded to 256 bytes.
+int64_t ctl_elems(int64_t n) { return (((int64_t)band_ctl_ints((int)n) + 63) / 64) * 16; }
+
+// Blocks of a k_band_step launch over a trailing matrix of order m.
+int step_grid(int64_t m) {
+  const int64_t nI = (m + ST - 1) / ST, T = nI * (nI + 1) / 2;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(2 * device_cus(), T));
+}
+
+}  // namespace
+
+bool tridiagonalise_band(const BandItem* it_all, int np_all, hipStream_t s) {
+  for (int g0 = 0; g0 < np_all; g0 += BAND_BATCH_MAX) {
+    const BandItem* it = it_all + g0;
+    const int np = std::min(BAND_BATCH_MAX, np_all - g0);
+    BandArgs A{};
+    int64_t nmax = 0;
+    for (int q = 0; q < np; ++q) {
+      const int64_t n = it[q].n, nb = (n + RB - 1) / RB;
+      BandProb& p = A.p[q];
+      p.M = it[q].M;
+      p.ld = it[q].ld;
+      p.n = (int)n;
+      p.ycs = (int)((n + ST - 1) / ST);
+      p.VW = it[q].b.VW;
+      p.Q1 = it[q].b.q1x;
+      p.X = p.Q1 + n * BW;
+      p.g1 = it[q].b.part;
+      p.g2 = p.g1 + nb * 256;
+      p.z = p.g2 + nb * 256;
+      p.pd = p.z + nb * 256;
+      p.sm = p.pd + nb * BW;
+      p.yp = it[q].b.yproj;
+      p.AB = it[q].b.big;
+      p.ctl = (int32_t*)(p.AB + band_elems(n));
+      p.Y = p.AB + band_elems(n) + ctl_elems(n);
+      p.dd = it[q].b.dd;
+      p.ee = it[q].b.ee;
+      p.info = it[q].info;
+      nmax = std::max(nmax, n);
+    }
+    // block ranges of a launch: `blocks(n)` blocks for the problems with panel k
+    auto ranges = [&](auto blocks) {
+      BandFirst f{};
+      int tot = 0;
+      for (int q = 0; q < BAND_BATCH_MAX; ++q) {
+        f.b[q] = tot;
+        if (q < np) tot += blocks((int64_t)A.p[q].n);
+      }
+      f.b[BAND_BATCH_MAX] = tot;
+      return f;
+    };
+    const BandFirst f0 = ranges([&](int64_t n) { return n > BW ? cdiv(n, RB) : 0; });
+    if (f0.b[BAND_BATCH_MAX] > 0)
+      BSE_LAUNCH(k_band_w, dim3(f0.b[BAND_BATCH_MAX]), dim3(NT), 0, s, A, f0, -1);
+    for (int k = 0; BW * (k + 1) < nmax; ++k) {
+      auto order = [&](int64_t n) { return n - BW * (k + 1); };  // trailing order
+      const BandFirst fr = ranges([&](int64_t n) { return order(n) > 0 ? cdiv(order(n), RB) : 0; });
+      const BandFirst fc = ranges(
+          [&](int64_t n) { return order(n) >= DIRECT_ROWS ? cdiv(order(n), RB) : 0; });
+      const BandFirst fs = ranges([&](int64_t n) { return order(n) > 0 ? step_grid(order(n)) : 0; });
+      BandFirst gs{};
+      for (int q = 0; q < np; ++q) gs.b[q] = fs.b[q + 1] - fs.b[q];
+      const dim3 rows(fr.b[BAND_BATCH_MAX]);
+      if (fc.b[BAND_BATCH_MAX] > 0)
+        BSE_LAUNCH(k_band_chol, dim3(fc.b[BAND_BATCH_MAX]), dim3(NT), 0, s, A, fc, k);
+      BSE_LAUNCH(k_band_panel, rows, dim3(NT), 0, s, A, fr, k);
+      BSE_LAUNCH(k_band_step, dim3(fs.b[BAND_BATCH_MAX]), dim3(STEP_THREADS), 0, s, A, fs, k);
+      BSE_LAUNCH(k_band_x, rows, dim3(NT), 0, s, A, fr, k, gs);
+      BSE_LAUNCH(k_band_w, rows, dim3(NT), 0, s, A, fr, k);
+    }
+    const BandFirst fp = ranges([&](int64_t n) { return (int)std::min<int64_t>(cdiv(n * ABS, 256), 1024); });
+    BSE_LAUNCH(k_band_pack, dim3(fp.b[BAND_BATCH_MAX]), dim3(256), 0, s, A, fp);
+    // sweeps in flight: one group per 2 CS BW columns of the band, with room
+    const int gmax = (int)std::max<int64_t>(cdiv(nmax - 1, CS), 1);
+    int64_t blocks = 0;
+    for (int q = 0; q < np; ++q) blocks += std::min<int64_t>(cdiv(A.p[q].n, 2 * CS * BW) + 2, gmax);
+    BSE_LAUNCH(k_band_chase, dim3((unsigned)std::min<int64_t>(blocks, device_cus())),
+               dim3(CH_THREADS), 0, s, A, np, gmax);
+  }
+  return hipGetLastError() == hipSuccess;
+}
+
+int64_t band_big_bytes(int64_t n) {
+  const int64_t slots = n > BW ? 2 * ((n + ST - 1) / ST) * n * BW : 0;
+  return 16 * (band_elems(n) + ctl_elems(n) + slots);
+}
+int64_t band_part_bytes(int64_t n) {
+  return 16 * (((n + RB - 1) / RB) * (3 * 256 + BW) + 512);
+}

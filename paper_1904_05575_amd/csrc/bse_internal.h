@@ -110,8 +110,8 @@ CholItem solve_chol_item(const bse_desc* d, void* H1, void* ws, int32_t* info);
 
 // The sweep's arguments for problem d in workspace ws (as solve_run passes
 // them; `project`: spectrum-only run with a probe).
-struct TrdItem;
-TrdItem solve_sweep_item(const bse_desc* d, void* H0, void* ws, bool project, int32_t* info);
+struct BandItem;
+BandItem solve_sweep_item(const bse_desc* d, void* H0, void* ws, bool project, int32_t* info);
 
 // screening.hip
 size_t screening_workspace(const bse_screen_desc* d);

@@ -5,9 +5,8 @@
 //
 // Per column c (local index i of its panel) two kernels run:
 //   k_trd_col   finishes reflector c-1: y = S v - V (W^H v) - W (V^H v) from
-//               the hemv kernel's partial sums, its W column, and H_{c-1}^H
-//               applied to an optional probe vector; then applies the panel's
-//               earlier reflectors to column c and writes block partial sums
+//               the hemv kernel's partial sums and its W column; then applies
+//               the panel's earlier reflectors to column c and writes block partial sums
 //               of |x|^2, V^H x, W^H x;
 //   k_trd_hemv  every block reduces |x|^2 (same order everywhere) and forms
 //               reflector c; the blocks then cover the lower triangle of the
@@ -35,7 +34,7 @@ constexpr int ROWS_A = 64;      // rows per block of the column kernel
 constexpr int COL_THREADS = 1024;
 constexpr int HT = 64;          // square tile of the hemv kernel
 constexpr int HV_THREADS = 1024; // hemv block: 16 wavefronts, 4 tile columns each
-constexpr int NVAL = 2 + 2 * TRD_NB;  // |x|^2, conj(x) y_probe, V^H x (i), W^H x (i)
+constexpr int NVAL = 1 + 2 * TRD_NB;  // |x|^2, V^H x (i), W^H x (i)
 
 // The hemv tiling of the trailing matrix (rows and columns b0..n-1) starts at
 // org = b0 rounded down to 8 elements (128 bytes), so that every column segment
@@ -106,11 +105,11 @@ BSE_DEV double2 sub_mulc(double2 x, double2 a, double2 b) {
   return make_double2(x.x - (a.x * b.x + a.y * b.y), x.y - (a.y * b.x - a.x * b.y));
 }
 
-BSE_DEV void trd_col_dev(
+__global__ __launch_bounds__(COL_THREADS) void k_trd_col(
     double2* __restrict__ M, int64_t ld, int n, double2* __restrict__ VW, double2* __restrict__ WV,
     int j0, int i, int has_new, const double2* __restrict__ hs, const double2* __restrict__ Y,
-    int ycs, int gprev, double2* __restrict__ partA, const double2* __restrict__ partB,
-    double2* __restrict__ yp, int bx) {
+    int ycs, int gprev, double2* __restrict__ partA, const double2* __restrict__ partB) {
+  const int bx = (int)blockIdx.x;
   constexpr int QP = COL_THREADS / ROWS_A;        // threads sharing one row
   constexpr int PER = TRD_NB / QP;                // panel columns per thread
   constexpr int YCH = 8;                          // y slots loaded per round
@@ -137,12 +136,11 @@ BSE_DEV void trd_col_dev(
   const double2 zero = make_double2(0.0, 0.0);
   const int rc = min(r, n - 1);
   static_assert(2 * TRD_NB == 64, "one wavefront stages V^H v | W^H v");
-  double2 svl = zero, x0 = zero, xv = zero, ypr = zero;
+  double2 svl = zero, x0 = zero, xv = zero;
   if (wid == 0) {
     svl = hs[HS_SVV + lane];
     x0 = M[rc + (int64_t)c * ld];
     xv = M[rc + (int64_t)max(c - 1, 0) * ld];
-    ypr = (yp ? yp : (const double2*)M)[rc];
   }
   // panel reflectors 0..i-2 on this row: the correction of y_{c-1}, step 2, step 3
   const int ipmax = max(i - 2, 0);
@@ -173,7 +171,7 @@ BSE_DEV void trd_col_dev(
 #pragma unroll
     for (int u = 0; u < PB; ++u) pbl[u] = partB[min(lane + 64 * u, max(nun - 1, 0))];
   }
-  const double2 tc = hs[HS_TAU], scal_p = hs[HS_SCAL], pdot = hs[HS_PDOT];
+  const double2 tc = hs[HS_TAU], scal_p = hs[HS_SCAL];
   // row c of the panel's earlier reflectors and the slots of y_{c-1}[c] (wavefront 1)
   constexpr int YC = 2;  // slots of row c per lane issued together
   double2 vcl = zero, wcl = zero, ycl[YC], scc = zero;
@@ -301,12 +299,6 @@ BSE_DEV void trd_col_dev(
       VW[r + (int64_t)(TRD_NB + i - 1) * N] = wprev_r;
       WV[r + (int64_t)(i - 1) * N] = wprev_r;
       WV[r + (int64_t)(TRD_NB + i - 1) * N] = vprev_r;
-      if (yp) {
-        // y_probe <- H^H y_probe = y_probe - conj(tau) (v^H y_probe) v
-        const double2 f = cmulc(tc, pdot);
-        ypr = csub(ypr, cmul(f, vprev_r));
-        yp[r] = ypr;
-      }
     }
     if (has_new) {
       vps[rr] = vprev_r;
@@ -331,11 +323,7 @@ BSE_DEV void trd_col_dev(
       }
       xs[rr] = tail ? x : make_double2(0.0, 0.0);
       const double2 s0 = wave_sum2_dpp(make_double2(tail ? cabs2(x) : 0.0, 0.0));
-      const double2 s1 = wave_sum2_dpp((tail && yp) ? cmulc(x, ypr) : make_double2(0.0, 0.0));
-      if (has_new && lane == 0) {  // the block's |x|^2 and conj(x) y_probe
-        partA[(int64_t)bx * NVAL + 0] = s0;
-        partA[(int64_t)bx * NVAL + 1] = s1;
-      }
+      if (has_new && lane == 0) partA[(int64_t)bx * NVAL] = s0;  // the block's |x|^2
     }
   }
   if (!has_new) return;
@@ -359,23 +347,14 @@ BSE_DEV void trd_col_dev(
         pv.y = wave_total63(pv.y);
         pw.x = wave_total63(pw.x);
         pw.y = wave_total63(pw.y);
-        // block partials, compact layout [|x|^2, conj(x) y, V^H x (i), W^H x (i)]
+        // block partials, compact layout [|x|^2, V^H x (i), W^H x (i)]
         if (lane == 63) {
-          partA[(int64_t)bx * NVAL + 2 + ip] = pv;
-          partA[(int64_t)bx * NVAL + 2 + i + ip] = pw;
+          partA[(int64_t)bx * NVAL + 1 + ip] = pv;
+          partA[(int64_t)bx * NVAL + 1 + i + ip] = pw;
         }
       }
     }
   }
-}
-
-__global__ __launch_bounds__(COL_THREADS) void k_trd_col(
-    double2* __restrict__ M, int64_t ld, int n, double2* __restrict__ VW, double2* __restrict__ WV,
-    int j0, int i, int has_new, const double2* __restrict__ hs, const double2* __restrict__ Y,
-    int ycs, int gprev, double2* __restrict__ partA, const double2* __restrict__ partB,
-    double2* __restrict__ yp) {
-  trd_col_dev(M, ld, n, VW, WV, j0, i, has_new, hs, Y, ycs, gprev, partA, partB, yp,
-              (int)blockIdx.x);
 }
 
 // Sum over the 16 lanes of each row of the wavefront (DPP within rows); every
@@ -400,8 +379,8 @@ BSE_DEV double row16_sum(double v) {
 // covers the next.  Within a piece no barrier is taken: each lane keeps its
 // rows' partial sums in registers, and each tile's column sums go from the
 // lanes straight to the slots.  A piece ends with one LDS reduction of its row
-// sums.  Block 0 also stores the reflector; V^H v, W^H v and conj(v) y_probe
-// for the next column kernel are spread over the blocks, one value each (the
+// sums.  Block 0 also stores the reflector; V^H v and W^H v for
+// the next column kernel are spread over the blocks, one value each (the
 // panel's share of y^H v follows from them in that kernel).  The column
 // kernel's partial sums are loaded before the tile prefetch so that the
 // reflector is not held up behind it.
@@ -410,12 +389,12 @@ BSE_DEV double row16_sum(double v) {
 // row 16 s + l % 16: four contiguous 256-byte column segments per
 // instruction.  A column's sum over the tile's rows is lane-local over s plus
 // one 16-lane DPP reduction serving four columns.
-BSE_DEV void trd_hemv_dev(
+__global__ __launch_bounds__(HV_THREADS) void k_trd_hemv(
     const double2* __restrict__ M, int64_t ld, int n, const double2* __restrict__ VW, int j0,
     int i, double2* __restrict__ hs, const double2* __restrict__ partA,
     double2* __restrict__ partB, double2* __restrict__ Y, int ycs,
-    double* __restrict__ dd, double* __restrict__ ee, double2* __restrict__ tau,
-    const double2* __restrict__ yp, int bx, int G) {
+    double* __restrict__ dd, double* __restrict__ ee, double2* __restrict__ tau) {
+  const int bx = (int)blockIdx.x, G = (int)gridDim.x;
   constexpr int NW = HV_THREADS / 64;     // 16 wavefronts
   constexpr int NL = 4;                   // matrix loads per lane per tile
   static_assert(NW * 4 == HT, "tile layout");
@@ -473,7 +452,7 @@ BSE_DEV void trd_hemv_dev(
   // wavefront 1, the column kernel's |x|^2 partials and this block's share of
   // the other partial sums (value t = 1 + bx, + G, ...)
   const int nbA = cdiv(n - c, ROWS_A);
-  const int nvals = 2 + 2 * i;
+  const int nvals = 1 + 2 * i;
   Pos C = pos_of(hemv_tile_start(T, G, bx));
   const double2 xv0 = xcol[min(org + C.I * HT + (tid & (HT - 1)), nlast)];
   // x on the rows of the next tile-row, loaded one piece ahead of its use
@@ -481,7 +460,7 @@ BSE_DEV void trd_hemv_dev(
   constexpr int PQ = 4;  // partial sums per lane issued together
   double2 pq0[PQ], pq1[PQ];
   const int t0 = 1 + bx;  // first value of wavefront 1
-  double2 ax = zero, vw1 = zero, yb0 = zero;
+  double2 ax = zero, vw1 = zero;
   if (wid == 1) {
     ax = xcol[b0];
     const int col1 = min(t0, NVAL - 1);
@@ -491,12 +470,8 @@ BSE_DEV void trd_hemv_dev(
       pq1[q] = partA[(int64_t)min(lane + 64 * q, nbA - 1) * NVAL + col1];
     }
     if (t0 < nvals) {
-      if (t0 >= 2) {
-        const int ip = (t0 - 2) % max(i, 1), w = (t0 - 2) / max(i, 1);
-        vw1 = VW[b0 + (int64_t)(w * TRD_NB + ip) * N];
-      } else if (yp) {
-        yb0 = yp[b0];
-      }
+      const int ip = (t0 - 1) % max(i, 1), w = (t0 - 1) / max(i, 1);
+      vw1 = VW[b0 + (int64_t)(w * TRD_NB + ip) * N];
     }
   }
   Pos Lq = C;
@@ -551,12 +526,12 @@ BSE_DEV void trd_hemv_dev(
       hs[HS_S00] = make_double2(M[b0 + (int64_t)b0 * ld].x, 0.0);
     }
     const double2 s1 = (t0 < nvals) ? colsum(pq1, min(t0, NVAL - 1)) : zero;  // uniform
-    // V^H v, W^H v of the panel and conj(v) y_probe: lane k takes value
+    // V^H v and W^H v of the panel: lane k takes value
     // t0 + k G (more than one only when there are fewer blocks than values,
     // i.e. for small trailing matrices)
     const int t = t0 + lane * G;
     if (t < nvals) {
-      double2 st = s1, e1 = vw1, y0 = yb0;
+      double2 st = s1, e1 = vw1;
       if (lane > 0) {
         st = zero;
         for (int b = 0; b < nbA; b += 4) {
@@ -567,16 +542,12 @@ BSE_DEV void trd_hemv_dev(
           for (int u = 0; u < 4; ++u)
             if (b + u < nbA) st = cadd(st, pv[u]);
         }
-        if (t >= 2) e1 = VW[b0 + (int64_t)(((t - 2) / i) * TRD_NB + (t - 2) % i) * N];
-        else if (yp) y0 = yp[b0];
+        e1 = VW[b0 + (int64_t)(((t - 1) / i) * TRD_NB + (t - 1) % i) * N];
       }
-      // v^H y_probe = y[c+1] + conj(scal) sum_{r >= c+2} conj(x_r) y_r
-      if (t == 1) {
-        if (yp) hs[HS_PDOT] = cadd(y0, cmulc(scal, st));
-      } else if (t < 2 + i) {
-        hs[HS_SVV + (t - 2)] = cadd(cconj(e1), cmul(scal, st));
+      if (t < 1 + i) {
+        hs[HS_SVV + (t - 1)] = cadd(cconj(e1), cmul(scal, st));
       } else {
-        hs[HS_SWV + (t - 2 - i)] = cadd(cconj(e1), cmul(scal, st));
+        hs[HS_SWV + (t - 1 - i)] = cadd(cconj(e1), cmul(scal, st));
       }
     }
   }
@@ -670,61 +641,6 @@ BSE_DEV void trd_hemv_dev(
   }
 }
 
-__global__ __launch_bounds__(HV_THREADS) void k_trd_hemv(
-    const double2* __restrict__ M, int64_t ld, int n, const double2* __restrict__ VW, int j0,
-    int i, double2* __restrict__ hs, const double2* __restrict__ partA,
-    double2* __restrict__ partB, double2* __restrict__ Y, int ycs,
-    double* __restrict__ dd, double* __restrict__ ee, double2* __restrict__ tau,
-    const double2* __restrict__ yp) {
-  trd_hemv_dev(M, ld, n, VW, j0, i, hs, partA, partB, Y, ycs, dd, ee, tau, yp, (int)blockIdx.x,
-               (int)gridDim.x);
-}
-
-// ---- the same sweep over several independent problems at once: one launch
-// per kernel and column step serves every problem still reducing (blockIdx.y
-// selects the problem; blocks past a problem's grid return at once).  The
-// kernel bodies are those of the single sweep, so with each problem's own hemv
-// grid (the default) every problem gets the values it gets on its own.
-// The problem that owns this block of a batched launch (a uniform scan of the
-// block ranges in the kernel arguments).
-BSE_DEV int batch_problem(const TrdFirst& f) {
-  int p = 0;
-  while (p + 1 < TRD_BATCH_MAX && (int)blockIdx.x >= f.b[p + 1]) ++p;
-  return p;
-}
-
-__global__ __launch_bounds__(COL_THREADS) void k_trd_col_b(TrdBatchArgs a, TrdFirst f, int jg,
-                                                           int i) {
-  const int pi = batch_problem(f);
-  const TrdProb p = a.p[pi];
-  const int bx = (int)blockIdx.x - f.b[pi];  // block within the problem's column kernel
-  const int n = p.n;
-  const int j0 = jg - p.shift;  // this problem's panel at global panel step jg
-  if (j0 < 0 || j0 >= n - 1) return;  // its sweep has not started or is over
-  const int jb = min(TRD_NB, n - 1 - j0);
-  if (i > jb) return;       // its last panel is shorter
-  const int c = j0 + i;
-  if (bx >= cdiv(n - c, ROWS_A)) return;
-  // uniform: readfirstlane keeps it (and all index arithmetic on it) scalar
-  const int gprev = __builtin_amdgcn_readfirstlane(c > 0 ? p.grids[c - 1] : 1);
-  trd_col_dev(p.M, p.ld, n, p.VW, p.WV, j0, i, i < jb ? 1 : 0, p.hs, p.Y, p.ycs, gprev, p.partA,
-              p.partB, p.yp, bx);
-}
-
-__global__ __launch_bounds__(HV_THREADS) void k_trd_hemv_b(TrdBatchArgs a, TrdFirst f, int jg,
-                                                           int i) {
-  const int pi = batch_problem(f);
-  const TrdProb p = a.p[pi];
-  const int bx = (int)blockIdx.x - f.b[pi];
-  const int n = p.n;
-  const int j0 = jg - p.shift;
-  if (j0 < 0 || j0 >= n - 1 || i >= min(TRD_NB, n - 1 - j0)) return;
-  const int G = f.b[pi + 1] - f.b[pi];  // the table's grid count for this step
-  if (bx >= G) return;
-  trd_hemv_dev(p.M, p.ld, n, p.VW, j0, i, p.hs, p.partA, p.partB, p.Y, p.ycs, p.dd, p.ee, p.tau,
-               p.yp, bx, G);
-}
-
 __global__ void k_trd_last(const double2* M, int64_t ld, int n, double* dd, const int32_t* info) {
   if (failed(info)) return;
   if (threadIdx.x == 0) dd[n - 1] = M[(n - 1) + (int64_t)(n - 1) * ld].x;
@@ -795,16 +711,16 @@ bool tridiagonalise(double2* M, int64_t n, int64_t ld, const TrdBufs& w, int32_t
     for (int i = 0; i < jb; ++i) {
       const int64_t c = j0 + i, m = n - trd_org((int)c + 1);  // order of the tiled block
       BSE_LAUNCH(k_trd_col, dim3(cdiv(n - c, ROWS_A)), dim3(COL_THREADS), 0, s, M, ld, (int)n, w.VW,
-                 w.WV, (int)j0, i, 1, w.hs, Y, ycs, gprev, partA, partB, w.yproj);
+                 w.WV, (int)j0, i, 1, w.hs, Y, ycs, gprev, partA, partB);
       const int g = hemv_grid(m);
       BSE_LAUNCH(k_trd_hemv, dim3(g), dim3(HV_THREADS), 0, s, M, ld, (int)n, w.VW, (int)j0, i,
-                 w.hs, partA, partB, Y, ycs, w.dd, w.ee, w.tau, w.yproj);
+                 w.hs, partA, partB, Y, ycs, w.dd, w.ee, w.tau);
       gprev = g;
     }
     // finish the panel's last reflector
     const int64_t cl = j0 + jb;
     BSE_LAUNCH(k_trd_col, dim3(cdiv(n - cl, ROWS_A)), dim3(COL_THREADS), 0, s, M, ld, (int)n,
-               w.VW, w.WV, (int)j0, jb, 0, w.hs, Y, ycs, gprev, partA, partB, w.yproj);
+               w.VW, w.WV, (int)j0, jb, 0, w.hs, Y, ycs, gprev, partA, partB);
     const int64_t t = j0 + jb;
     if (t < n) {
       ZgemmParams g;  // S[t:, t:] -= [V W] [W V]^H
@@ -831,237 +747,5 @@ bool tridiagonalise(double2* M, int64_t n, int64_t ld, const TrdBufs& w, int32_t
     }
   }
   BSE_LAUNCH(k_trd_last, dim3(1), dim3(64), 0, s, M, ld, (int)n, w.dd, info);
-  return hipGetLastError() == hipSuccess;
-}
-
-namespace {
-
-// Device pointers of problem `it`'s share of the partial-sum space.
-void trd_parts(const TrdItem& it, double2** partA, double2** partB, double2** Y) {
-  *partA = it.w.part;
-  *partB = it.w.part + ((it.n + ROWS_A - 1) / ROWS_A + 1) * NVAL;
-  *Y = *partB + hemv_tiles_max(it.n) + 1;
-}
-
-// Global panel step at which each problem of a group starts its sweep: 0 for
-// all (BSE_TUNE_BATCH_ALIGN choice 0), or late by the largest multiple of
-// TRD_NB that keeps it within the largest problem's steps (choice 1), so that
-// the sweeps end together and every step reduces about the same bytes.
-std::vector<int> batch_shifts(const TrdItem* it, int np) {
-  int64_t nmax = 0;
-  for (int p = 0; p < np; ++p) nmax = std::max(nmax, it[p].n);
-  const int align = tune_choice(BSE_TUNE_BATCH_ALIGN, nmax, 0);
-  std::vector<int> sh(np, 0);
-  if (align == 1)
-    for (int p = 0; p < np; ++p) sh[p] = (int)(((nmax - it[p].n) / TRD_NB) * TRD_NB);
-  return sh;
-}
-
-// Blocks of every problem's hemv launch for its reflector c, c = 0 .. n - 2: by
-// default hemv_grid() blocks, as in the problem's own sweep; in shared mode the
-// launch of a global step has `per_cu` blocks per compute unit in all (at most
-// one per CU per problem reducing at that step), each such problem getting a
-// share proportional to its tiles (at least one, at most one per tile), so that
-// all blocks take runs of about equal length.
-std::vector<std::vector<int32_t>> batch_grids(const TrdItem* it, int np) {
-  int64_t nmax = 0;
-  for (int p = 0; p < np; ++p) nmax = std::max(nmax, it[p].n);
-  const int per_cu = tune_choice(BSE_TUNE_BATCH_SWEEP, nmax, 0);
-  const std::vector<int> sh = batch_shifts(it, np);
-  auto tiles = [](int64_t n, int64_t c) {
-    const int64_t nI = (n - trd_org((int)c + 1) + HT - 1) / HT;
-    return nI * (nI + 1) / 2;
-  };
-  std::vector<std::vector<int32_t>> g(np);
-  for (int p = 0; p < np; ++p) g[p].assign((size_t)std::max<int64_t>(it[p].n - 1, 0), 1);
-  // global column cg: problem p reduces its column cg - shift_p (if it has one)
-  for (int64_t cg = 0; cg + 1 < nmax; ++cg) {
-    double sum = 0.0;
-    int nact = 0;  // problems reducing at this step
-    for (int p = 0; p < np; ++p) {
-      const int64_t c = cg - sh[p];
-      if (c >= 0 && c + 1 < it[p].n) {
-        sum += (double)tiles(it[p].n, c);
-        ++nact;
-      }
-    }
-    // at most one block per CU per problem reducing: a problem alone keeps the
-    // one-per-CU grid of its own sweep
-    const double total = (double)std::min(per_cu, std::max(nact, 1)) * device_cus();
-    for (int p = 0; p < np; ++p) {
-      const int64_t c = cg - sh[p];
-      if (c < 0 || c + 1 >= it[p].n) continue;
-      const int64_t T = tiles(it[p].n, c);
-      int64_t G;
-      if (per_cu == 0) {
-        G = hemv_grid(it[p].n - trd_org((int)c + 1));
-      } else {
-        G = std::llround(total * (double)T / sum);
-        G = std::max<int64_t>(1, std::min(G, T));
-      }
-      g[p][c] = (int32_t)G;
-    }
-  }
-  return g;
-}
-
-// The block ranges of the column-kernel and hemv launches of step (jg, i): per
-// problem reducing at that step its column grid and its hemv grid, in problem
-// order (compact grids: no block of a launch is idle).
-struct StepGrids {
-  TrdFirst col{}, hemv{};
-};
-StepGrids step_grids(const TrdItem* it, int np, const std::vector<std::vector<int32_t>>& grids,
-                     const std::vector<int>& sh, int64_t jg, int i) {
-  StepGrids g;
-  int nc = 0, nh = 0;
-  for (int p = 0; p < TRD_BATCH_MAX; ++p) {
-    g.col.b[p] = nc;
-    g.hemv.b[p] = nh;
-    if (p >= np) continue;
-    const int64_t n = it[p].n, j0 = jg - sh[p];
-    if (j0 < 0 || j0 >= n - 1) continue;
-    const int jb = (int)std::min<int64_t>(TRD_NB, n - 1 - j0);
-    if (i > jb) continue;
-    const int64_t c = j0 + i;
-    nc += cdiv(n - c, ROWS_A);
-    if (i < jb) nh += (int)grids[p][c];
-  }
-  g.col.b[TRD_BATCH_MAX] = nc;
-  g.hemv.b[TRD_BATCH_MAX] = nh;
-  return g;
-}
-
-}  // namespace
-
-size_t trd_batch_table_bytes(const int64_t* n, int np) {
-  size_t b = 0;
-  for (int p = 0; p < np; ++p) b += (size_t)std::max<int64_t>(n[p], 1) * sizeof(int32_t);
-  return b;
-}
-
-namespace {
-// Offset (in int32 entries) of problem p's grid counts in the table.
-std::vector<size_t> grid_offsets(const TrdItem* it, int np) {
-  std::vector<size_t> off(np + 1, 0);
-  for (int p = 0; p < np; ++p) off[p + 1] = off[p] + (size_t)std::max<int64_t>(it[p].n, 1);
-  return off;
-}
-}  // namespace
-
-bool trd_batch_table(const TrdItem* it, int np, void* dev, size_t bytes) {
-  if (np <= 0 || !dev) return false;
-  const std::vector<size_t> off = grid_offsets(it, np);
-  if (bytes < off[np] * sizeof(int32_t)) return false;
-  std::vector<int32_t> host(off[np], 0);
-  for (int g0 = 0; g0 < np; g0 += TRD_BATCH_MAX) {  // groups as tridiagonalise_batch forms them
-    const int ng = std::min(TRD_BATCH_MAX, np - g0);
-    const auto grids = batch_grids(it + g0, ng);
-    for (int p = 0; p < ng; ++p)
-      std::copy(grids[p].begin(), grids[p].end(), host.begin() + off[g0 + p]);
-  }
-  return hipMemcpy(dev, host.data(), off[np] * sizeof(int32_t), hipMemcpyHostToDevice) ==
-         hipSuccess;
-}
-
-bool tridiagonalise_batch(const TrdItem* it_all, int np_all, const void* dev, hipStream_t s) {
-  const std::vector<size_t> off = grid_offsets(it_all, np_all);
-  for (int g0 = 0; g0 < np_all; g0 += TRD_BATCH_MAX) {
-    const TrdItem* it = it_all + g0;
-    const int np = std::min(TRD_BATCH_MAX, np_all - g0);
-    const auto grids = batch_grids(it, np);  // as written into the table
-    const std::vector<int> sh = batch_shifts(it, np);
-    TrdBatchArgs A{};
-    int64_t nmax = 0;
-    for (int p = 0; p < np; ++p) {
-      const TrdItem& q = it[p];
-      TrdProb& t = A.p[p];
-      t.M = q.M;
-      t.ld = q.ld;
-      t.n = (int)q.n;
-      t.ycs = (int)ycs_of(q.n);
-      t.VW = q.w.VW;
-      t.WV = q.w.WV;
-      t.hs = q.w.hs;
-      trd_parts(q, &t.partA, &t.partB, &t.Y);
-      t.yp = q.w.yproj;
-      t.tau = q.w.tau;
-      t.dd = q.w.dd;
-      t.ee = q.w.ee;
-      t.grids = (const int32_t*)dev + off[g0 + p];
-      t.shift = sh[p];
-      nmax = std::max(nmax, q.n);
-    }
-    for (int64_t jg = 0; jg < nmax - 1; jg += TRD_NB) {  // global panel steps
-      int jbmax = 0;
-      for (int p = 0; p < np; ++p) {
-        const TrdItem& q = it[p];
-        const int64_t j0 = jg - sh[p];
-        if (j0 < 0 || j0 >= q.n - 1) continue;
-        const int jb = (int)std::min<int64_t>(TRD_NB, q.n - 1 - j0);
-        jbmax = std::max(jbmax, jb);
-        if (jb < TRD_NB)
-          BSE_LAUNCH(k_trd_zero_cols, dim3(256), dim3(256), 0, s, q.w.VW, q.w.WV, q.n, jb);
-      }
-      for (int i = 0; i <= jbmax; ++i) {
-        const StepGrids g = step_grids(it, np, grids, sh, jg, i);
-        const int ncol = g.col.b[TRD_BATCH_MAX], nhemv = g.hemv.b[TRD_BATCH_MAX];
-        if (ncol > 0)
-          BSE_LAUNCH(k_trd_col_b, dim3(ncol), dim3(COL_THREADS), 0, s, A, g.col, (int)jg, i);
-        if (nhemv > 0)
-          BSE_LAUNCH(k_trd_hemv_b, dim3(nhemv), dim3(HV_THREADS), 0, s, A, g.hemv, (int)jg, i);
-      }
-      // S[t:, t:] -= [V W] [W V]^H for every problem, as one grouped GEMM per
-      // tuned tile (each item with the tile the single sweep gives it)
-      std::vector<ZgemmItem> up;
-      std::vector<int> tiles;
-      for (int p = 0; p < np; ++p) {
-        const TrdItem& q = it[p];
-        const int64_t j0 = jg - sh[p];
-        if (j0 < 0 || j0 >= q.n - 1) continue;
-        const int64_t t = j0 + std::min<int64_t>(TRD_NB, q.n - 1 - j0);
-        const int64_t n = q.n;
-        if (t >= n) continue;
-        ZgemmItem g;
-        g.M = (int)(n - t);
-        g.N = (int)(n - t);
-        g.K = 2 * TRD_NB;
-        g.A = q.w.VW + t;
-        g.a_rs = 1;
-        g.a_cs = n;
-        g.B = q.w.WV + t;
-        g.b_rs = n;
-        g.b_cs = 1;
-        g.C = q.M + t + t * q.ld;
-        g.c_rs = 1;
-        g.c_cs = q.ld;
-        g.info = q.info;
-        up.push_back(g);
-        tiles.push_back(tune_choice(BSE_TUNE_GEMM_HER2K, n, 0));
-      }
-      std::vector<char> done(up.size(), 0);
-      std::vector<ZgemmItem> grp;
-      for (size_t a = 0; a < up.size(); ++a) {
-        if (done[a]) continue;
-        grp.clear();
-        for (size_t b = a; b < up.size(); ++b)
-          if (!done[b] && tiles[b] == tiles[a]) {
-            grp.push_back(up[b]);
-            done[b] = 1;
-          }
-        ZgemmParams base;
-        base.conjB = 1;
-        base.c_uplo = 2;  // lower triangle only
-        base.alpha = make_double2(-1.0, 0.0);
-        base.beta = 1.0;
-        base.tag = "zgemm_her2k";
-        base.tile = tiles[a];
-        if (zgemm_group(base, grp.data(), (int)grp.size(), s) != hipSuccess) return false;
-      }
-    }
-    for (int p = 0; p < np; ++p)
-      BSE_LAUNCH(k_trd_last, dim3(1), dim3(64), 0, s, it[p].M, it[p].ld, (int)it[p].n,
-                 it[p].w.dd, it[p].info);
-  }
   return hipGetLastError() == hipSuccess;
 }

@@ -1663,8 +1663,15 @@ bse_status solve_run(const bse_desc* d, void* H0v, void* H1v, double* E, void* X
       }
     }
   }  // SOLVE_PRE2
-  TrdBufs tb{w.VW, w.WV, w.ybuf, w.hs, w.part, w.dd, w.ee, w.tau, project ? w.yvec : nullptr};
-  if ((phase & SOLVE_SWEEP) && !tridiagonalise(Hm, n, ld, tb, info, s)) return BSE_ERR_HIP;
+  if (phase & SOLVE_SWEEP) {
+    if (XpY) {  // the reflectors are kept for the back-transform
+      TrdBufs tb{w.VW, w.WV, w.ybuf, w.hs, w.part, w.dd, w.ee, w.tau};
+      if (!tridiagonalise(Hm, n, ld, tb, info, s)) return BSE_ERR_HIP;
+    } else {
+      const BandItem it = solve_sweep_item(d, H0v, ws, project, info);
+      if (!tridiagonalise_band(&it, 1, s)) return BSE_ERR_HIP;
+    }
+  }
   if (!(phase & SOLVE_POST)) return BSE_OK;
   BSE_LAUNCH(k_tri_prep, dim3(1), dim3(1024), 0, s, w.dd, w.ee, (int)n, w.ds, w.es, w.e2s,
              w.stat, info);
@@ -1730,13 +1737,15 @@ bse_status solve_run(const bse_desc* d, void* H0v, void* H1v, double* E, void* X
   return hipGetLastError() == hipSuccess ? BSE_OK : BSE_ERR_HIP;
 }
 
-TrdItem solve_sweep_item(const bse_desc* d, void* H0, void* ws, bool project, int32_t* info) {
+BandItem solve_sweep_item(const bse_desc* d, void* H0, void* ws, bool project, int32_t* info) {
   const SolveWs w = carve(d, ws);
-  TrdItem it;
+  BandItem it;
   it.M = (double2*)H0;
   it.n = (int64_t)d->nk * d->nv * d->nc;
   it.ld = d->ld;
-  it.w = TrdBufs{w.VW, w.WV, w.ybuf, w.hs, w.part, w.dd, w.ee, w.tau, project ? w.yvec : nullptr};
+  // free during the reduction: the squared form's T1 and the eigenvector
+  // stage's arrays (adjacent), the Cholesky's and the back-transform's panels
+  it.b = BandBufs{w.VW, w.W2, w.W1, w.Wk, w.dd, w.ee, project ? w.yvec : nullptr};
   it.info = info;
   return it;
 }

@@ -9,9 +9,8 @@ constexpr int TRD_NB = 32;  // Householder panel width
 //   [0] scal = 1/(alpha_x - beta) of the current reflector, [1] tau,
 //   [2] S[b0][b0], the first diagonal element of the trailing matrix the
 //       current reflector multiplies (b0 = c + 1),
-//   [3] v^H y_probe of the current reflector,
 //   [4, 4 + TRD_NB) V^H v and [4 + TRD_NB, 4 + 2 TRD_NB) W^H v over the panel
-constexpr int HS_SCAL = 0, HS_TAU = 1, HS_S00 = 2, HS_PDOT = 3, HS_SVV = 4, HS_SWV = 4 + TRD_NB,
+constexpr int HS_SCAL = 0, HS_TAU = 1, HS_S00 = 2, HS_SVV = 4, HS_SWV = 4 + TRD_NB,
               HS_SIZE = 4 + 2 * TRD_NB;
 
 struct TrdBufs {
@@ -23,57 +22,36 @@ struct TrdBufs {
   double* dd;       // n   diagonal of T
   double* ee;       // n-1 off-diagonal of T
   double2* tau;     // n-1 reflector scalars
-  double2* yproj;   // optional: vector y, replaced by Q^H y
 };
 
 int64_t trd_part_elems(int64_t n);
 bool tridiagonalise(double2* M, int64_t n, int64_t ld, const TrdBufs& w, int32_t* info,
                     hipStream_t s);
 
-// One problem of a batched sweep: its matrix, order, leading dimension,
-// buffers and status word (each problem has its own; none may alias another's).
-struct TrdItem {
+// Two-stage reduction (band.hip): dense to a band of half width BAND_W, then to
+// tridiagonal form.  For solves that form no eigenvectors.
+constexpr int BAND_W = 16;
+constexpr int BAND_BATCH_MAX = 16;  // problems per launch
+constexpr int CHASE_SWEEPS = 4;  // sweeps per block of the second stage
+
+struct BandBufs {
+  double2* VW;      // n x 4 BAND_W
+  double2* q1x;     // n x 2 BAND_W
+  double2* part;    // band_part_bytes(n)
+  double2* big;     // band_big_bytes(n)
+  double* dd;       // n   diagonal of T
+  double* ee;       // n-1 off-diagonal of T
+  double2* yproj;   // optional: vector y, replaced by Q^H y
+};
+struct BandItem {
   double2* M;
   int64_t n, ld;
-  TrdBufs w;
+  BandBufs b;
   int32_t* info;
 };
-
-// Per-problem arguments of the batched kernels (grids[c] = blocks of the hemv
-// launch for reflector c, in device memory written by trd_batch_table; shift =
-// the global panel step, a multiple of TRD_NB, at which this problem's sweep
-// starts: column c of the problem is reduced at global column shift + c).  They
-// travel by value in the kernel arguments, up to TRD_BATCH_MAX problems per
-// launch, so that the compiler knows every pointer to be device memory.
-struct TrdProb {
-  double2* M;
-  int64_t ld;
-  int n, ycs;
-  double2 *VW, *WV, *hs, *Y, *partA, *partB, *yp, *tau;
-  double *dd, *ee;
-  const int32_t* grids;
-  int shift;
-};
-constexpr int TRD_BATCH_MAX = 16;
-struct TrdBatchArgs {
-  TrdProb p[TRD_BATCH_MAX];
-};
-// A batched launch's blocks, problem after problem: problem p owns blocks
-// [b[p], b[p+1]); entries past the group's last problem equal the total, so a
-// problem with nothing to do at a step owns no block.
-struct TrdFirst {
-  int32_t b[TRD_BATCH_MAX + 1];
-};
-
-// Bytes of the device table (the hemv grid counts of every step) for problems
-// of orders n[0..np-1].
-size_t trd_batch_table_bytes(const int64_t* n, int np);
-// Fill the table `dev` (trd_batch_table_bytes long) for these problems: a
-// blocking host-to-device copy, made before the sweep is enqueued or captured.
-bool trd_batch_table(const TrdItem* it, int np, void* dev, size_t bytes);
-// The sweep of every problem at once (in groups of up to TRD_BATCH_MAX): per
-// column step one column-kernel launch and one hemv launch serve all problems
-// of a group still reducing.  With the per-problem grid choice each problem's
-// values are those of tridiagonalise() on its own; with blocks shared among the
-// problems they differ from those in rounding order only.
-bool tridiagonalise_batch(const TrdItem* it, int np, const void* dev, hipStream_t s);
+int64_t band_big_bytes(int64_t n);
+int64_t band_part_bytes(int64_t n);
+// Every problem's matrix (lower triangle) to tridiagonal form, in groups of up
+// to BAND_BATCH_MAX problems per launch; each problem's values do not depend on
+// what else is in the batch.
+bool tridiagonalise_band(const BandItem* it, int np, hipStream_t s);

@@ -1,7 +1,7 @@
 """Autotuner of the library's tile choices (run on the GPU; writes a JSON table).
 
     python -m paper_1904_05575_amd.tune [--out PATH] [--reps 2]
-                                        [--hemv-only | --gemm-site SITE | --batch-sweep-only]
+                                        [--hemv-only | --gemm-site SITE]
 
 For every tunable call site of the FP64 path (see bse_tune_entry in
 include/bse.h) the tuner builds and solves seeded synthetic problems of the
@@ -13,12 +13,8 @@ fastest:
     per-pair contraction, the exchange term and the eigenvector path's
     products (timed in a solve with X+Y and X-Y), per problem order n;
   * the least number of tiles per block of the Householder hemv kernel
-    (1, 2, 4, 8), per bucket of the trailing order m, on the largest problem;
-  * the blocks of the batched sweep's hemv launches (each problem's own grid,
-    or 1, 2, 4 per compute unit shared among the problems) together with when
-    the problems' sweeps start (all at once, or late so that they end
-    together), timed on the batch16 graph, for batches up to its largest
-    order.
+    (1, 2, 4, 8), per bucket of the trailing order m, on the largest problem
+    (a solve with X+Y).
 `load()` installs the table in the library (Problem and Batch call it once).
 """
 from __future__ import annotations
@@ -43,14 +39,10 @@ GEMM_SITES = {  # site -> (candidates, kernel tags timed)
     "gemm_vectors": ((32, 64), ("zgemm_bt_vhz", "zgemm_bt_update", "zgemm_recon",
                                 "zgemm_trsm", "zgemm_trsm_in")),
 }
-VECTOR_SITES = ("gemm_vectors",)  # timed in a solve that forms X+Y and X-Y
+VECTOR_SITES = ("gemm_vectors", "gemm_her2k")  # timed in a solve that forms X+Y and X-Y
 HEMV_BUCKETS = (1024, 2048, 3072, 4096, 8192)  # upper bounds of the trailing order m
 HEMV_UNITS = (1, 2, 4, 8)
 HEMV_TAGS = ("k_trd_hemv", "k_trd_col")
-BATCH_SWEEP_CHOICES = (0, 1, 2, 4)
-BATCH_ALIGN_CHOICES = (0, 1)
-BATCH_SITES = ("batch_sweep", "batch_align")
-BATCH_WORKLOAD = "batch16_k6_g89"
 
 _loaded = False
 
@@ -94,66 +86,6 @@ def _time_sites(P, tags, reps, vectors=False):
     return best
 
 
-def _tune_batch_sweep(base, reps, measured):
-    """Time the batch16 graph (one branch per problem, FP64) under each pair of
-    batched-sweep choices (hemv blocks; sweeps starting together or ending
-    together) with the entries `base` installed; returns the two table entries."""
-    import torch
-    from bse_synth import BATCHES, make_batch_inputs
-    from .batch import Batch
-
-    load()  # Batch() installs the stored table once; do it before the candidates
-    ms = make_batch_inputs(BATCHES[BATCH_WORKLOAD])
-    nmax = max(d["workload"].n for d in ms)
-    times = {}
-    for al in BATCH_ALIGN_CHOICES:
-        for c in BATCH_SWEEP_CHOICES:
-            L.bse_tune_set(base + [(L.TUNE_SITES["batch_sweep"], nmax, c),
-                                   (L.TUNE_SITES["batch_align"], nmax, al)])
-            B = Batch(ms, precision="fp64", nbranch=len(ms))
-            B.run()
-            torch.cuda.synchronize()
-            best = None
-            for _ in range(reps):
-                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-                a.record()
-                B.run()
-                b.record()
-                torch.cuda.synchronize()
-                t = a.elapsed_time(b)
-                best = t if best is None else min(best, t)
-            B.results()  # raises on a device error
-            B.close()
-            del B
-            torch.cuda.empty_cache()
-            times[(c, al)] = best
-    c, al = min(times, key=times.get)
-    measured[f"batch_sweep@{BATCH_WORKLOAD}"] = {f"{k[0]}/align{k[1]}": round(v, 2)
-                                                 for k, v in times.items()}
-    print(f"[tune] {BATCH_WORKLOAD} batch_sweep/align: {times} -> {(c, al)}", file=sys.stderr,
-          flush=True)
-    return [{"site": "batch_sweep", "size_max": nmax, "choice": c},
-            {"site": "batch_align", "size_max": nmax, "choice": al}]
-
-
-def run_batch_sweep_only(out: str, reps: int = 2) -> dict:
-    """Re-tune only the batched sweep's choices, keeping the table's other entries."""
-    with open(TABLE) as f:
-        tab = json.load(f)
-    keep = [e for e in tab["entries"] if e["site"] not in BATCH_SITES]
-    base = [(L.TUNE_SITES[e["site"]], int(e["size_max"]), int(e["choice"])) for e in keep]
-    measured = {k: v for k, v in tab.get("measured_ms", {}).items()
-                if not k.startswith("batch_sweep@")}
-    t0 = time.time()
-    new = _tune_batch_sweep(base, reps, measured)
-    L.bse_tune_set([])
-    tab["entries"], tab["measured_ms"] = keep + new, measured
-    tab["seconds_batch_sweep"] = round(time.time() - t0, 1)
-    with open(out, "w") as f:
-        json.dump(tab, f, indent=1)
-    return tab
-
-
 def run_hemv_only(out: str, reps: int = 2) -> dict:
     """Re-tune only the hemv buckets, keeping the table's other entries (which
     stay installed while the hemv choices are timed)."""
@@ -178,7 +110,7 @@ def run_hemv_only(out: str, reps: int = 2) -> dict:
         times = {}
         for K in HEMV_UNITS:
             L.bse_tune_set(base + [(L.TUNE_SITES["hemv_unit"], hi, K)])
-            times[K] = _time_sites(P, HEMV_TAGS, reps)
+            times[K] = _time_sites(P, HEMV_TAGS, reps, True)
         best = min(times, key=times.get)
         entries.append({"site": "hemv_unit", "size_max": hi, "choice": best})
         measured[f"hemv_unit@m<={hi}"] = {str(k): round(v, 4) for k, v in times.items()}
@@ -271,7 +203,7 @@ def run(out: str, reps: int = 2) -> dict:
         times = {}
         for K in HEMV_UNITS:
             L.bse_tune_set([(L.TUNE_SITES["hemv_unit"], hi, K)])
-            times[K] = _time_sites(P, HEMV_TAGS, reps)
+            times[K] = _time_sites(P, HEMV_TAGS, reps, True)
         best = min(times, key=times.get)
         entries.append({"site": "hemv_unit", "size_max": hi, "choice": best})
         measured[f"hemv_unit@m<={hi}"] = {str(k): round(v, 4) for k, v in times.items()}
@@ -279,9 +211,6 @@ def run(out: str, reps: int = 2) -> dict:
         lo = hi
     del P
     torch.cuda.empty_cache()
-    base = [(L.TUNE_SITES[e["site"]], int(e["size_max"]), int(e["choice"])) for e in entries]
-    entries += _tune_batch_sweep(base, reps, measured)
-    L.bse_tune_set([])
     tab = {"device": torch.cuda.get_device_name(0), "entries": entries,
            "measured_ms": measured, "seconds": round(time.time() - t0, 1),
            "workloads": {"sizes": sizes, "hemv": big["workload"].name}}
@@ -298,13 +227,9 @@ def main() -> int:
                     help="re-tune the hemv buckets only, keeping the other entries")
     ap.add_argument("--gemm-site", choices=sorted(GEMM_SITES),
                     help="re-tune one GEMM site only, keeping the other entries")
-    ap.add_argument("--batch-sweep-only", action="store_true",
-                    help="re-tune the batched sweep's choice only, keeping the other entries")
     args = ap.parse_args()
     if args.hemv_only:
         tab = run_hemv_only(args.out, args.reps)
-    elif args.batch_sweep_only:
-        tab = run_batch_sweep_only(args.out, args.reps)
     elif args.gemm_site:
         tab = run_gemm_site_only(args.out, args.gemm_site, args.reps)
     else:
