@@ -10,10 +10,10 @@
 //   k_band_chol   R1 from the Gram matrix of the panel P = S[t:, j0:j0+BW]
 //                 (Cholesky), Q1 = P R1^-1, Gram partials of Q1
 //   k_band_panel  R2 from the Gram matrix of Q1 (the second Cholesky pass makes
-//                 Q = Q1 R2^-1 orthonormal to rounding), then the Householder
-//                 form of Q: Q - [D; 0] = V U' (LU without pivoting, D unit
-//                 modulus against the pivot's phase), H = I - V T V^H with
-//                 T = -U' D^* V_top^-H, and P = H [D R2 R1; 0]
+//                 Q = Q1 R2^-1 orthonormal to rounding), then the reflector whose
+//                 first columns are Q's: with D a diagonal of modulus one that
+//                 opposes the pivots of Q_top - D, V = Q - [D; 0], H = I - V T V^H,
+//                 T = -D^* (Q_top - D)^-H, and P = H [D R2 R1; 0]
 //   k_band_step   the trailing triangle S -= V W^H + W V^H of the previous
 //                 panel and, from the same registers, the partial products of
 //                 X = S V with this panel's V
@@ -41,11 +41,7 @@ namespace {
 
 constexpr int BW = BAND_W;
 static_assert(BW == 16, "one 16 x 16 matrix-core tile per block of the band");
-constexpr int RB = 128;           // rows per block of the panel kernels
-constexpr int NT = 512;           // threads of the panel kernels: 8 wavefronts of 16 rows
-constexpr int NWV = NT / 64;
 constexpr int DIRECT_ROWS = 64;   // panels with fewer rows are factored column by column
-constexpr int ST = 64;            // tile edge of k_band_step
 constexpr int LDT = BW + 1;       // padded row of a 16 x 16 tile in LDS
 constexpr int ABS = 2 * BW + 2;   // band storage per column: 2 BW diagonals, the probe, one spare
                                   // (in LDS a row of the band then steps by 2 BW + 1 values, over
@@ -53,6 +49,19 @@ constexpr int ABS = 2 * BW + 2;   // band storage per column: 2 BW diagonals, th
 
 // Complex elements of the stored band, rounded to 256 bytes.
 __host__ __device__ inline int64_t band_elems(int64_t n) { return (n * ABS + 15) & ~(int64_t)15; }
+
+// Rows of a block of the panel kernels (one wavefront per 16 rows) for a trailing
+// matrix of order m: 64 give each wavefront a SIMD of its own; beyond 4096 rows
+// 128, since every block reads all blocks' 16 x 16 partial sums.
+__host__ __device__ inline int panel_rows(int64_t m) { return m > 4096 ? 128 : 64; }
+__host__ __device__ inline int panel_blocks(int64_t m) { return cdiv(m, panel_rows(m)); }
+
+// Tile edge of k_band_step at trailing order m: below 512 a launch of 64 x 64 tiles
+// leaves most compute units idle (n = 324: 17.8 us per launch, 11.6 with 32 x 32);
+// above it the smaller tile gains in that kernel what its slots cost k_band_x (n =
+// 2048, both kernels, small tiles up to 512, 768, 1024, 1408: 4.76, 4.76, 4.80, 4.94 ms).
+constexpr int STEP_SMALL = 512;
+__host__ __device__ inline int step_tile(int64_t m) { return m > STEP_SMALL ? 64 : 32; }
 
 __host__ __device__ inline int band_ctl_ints(int n) { return 2 + n / CHASE_SWEEPS + 1; }
 
@@ -189,26 +198,38 @@ BSE_DEV void wave_lds_sync() {
 }
 
 // Sum of `nb` blocks' 16 x 16 partials into out (256 values, LDS); tmp: 256
-// values.  Two threads per value (even and odd blocks), the order fixed.
+// values.  NW = 8: two threads per value (even and odd blocks); the order is fixed.
+template <int NW>
 BSE_DEV void sum_partials(const double2* __restrict__ part, int nb, double2* out, double2* tmp) {
+  constexpr int ST2 = NW / 4;
   const int e = threadIdx.x & 255, h = threadIdx.x >> 8;
   double2 s = czero();
   int b = h;
-  for (; b + 14 < nb; b += 16) {
-    double2 v[8];
+  for (; b + 15 * ST2 < nb; b += 16 * ST2) {
+    double2 v[16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(b + 2 * u) * 256 + e];
+    for (int u = 0; u < 16; ++u) v[u] = part[(int64_t)(b + ST2 * u) * 256 + e];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s = cadd(s, v[u]);
+    for (int u = 0; u < 16; ++u) s = cadd(s, v[u]);
   }
-  for (; b < nb; b += 2) s = cadd(s, part[(int64_t)b * 256 + e]);
-  if (h) tmp[e] = s;
-  __syncthreads();
-  if (!h) out[e] = cadd(s, tmp[e]);
+  if (b < nb) {  // the rest, together (clamped, masked)
+    double2 v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = part[(int64_t)min(b + ST2 * u, nb - 1) * 256 + e];
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (b + ST2 * u < nb) s = cadd(s, v[u]);
+  }
+  if (NW == 8) {
+    if (h) tmp[e] = s;
+    __syncthreads();
+  }
+  if (!h) out[e] = NW == 8 ? cadd(s, tmp[e]) : s;
   __syncthreads();
 }
 
 // Block-wide sum of the wavefronts' 16 x 16 results into part[0..255].
+template <int NW>
 BSE_DEV void reduce_tiles(const Acc& a, double2* red, double2* __restrict__ part) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
@@ -218,7 +239,7 @@ BSE_DEV void reduce_tiles(const Acc& a, double2* red, double2* __restrict__ part
   if (threadIdx.x < 256) {
     double2 s = czero();
 #pragma unroll
-    for (int w = 0; w < NWV; ++w) s = cadd(s, red[w * 256 + threadIdx.x]);
+    for (int w = 0; w < NW; ++w) s = cadd(s, red[w * 256 + threadIdx.x]);
     part[threadIdx.x] = s;
   }
 }
@@ -229,36 +250,52 @@ struct StepShare {  // values of the current elimination step, two steps' buffer
 };
 
 // Cholesky factor and its inverse of the 16 x 16 Hermitian matrix in G (LDS,
-// row-major), by the whole block: threads 0..255 eliminate the matrix, 256..511
-// the identity beside it, one barrier per column.  L and Li: LDS, rows of LDT.
-// Returns false (uniformly) when a pivot is not above tol times its diagonal.
+// row-major), by the block's first 256 threads, each with one element of the
+// matrix and one of the identity beside it; one barrier per column.  L and Li:
+// LDS, rows of LDT.  Returns false (uniformly) when a pivot is not above tol
+// times its diagonal.
 BSE_DEV bool chol_inv(const double2* G, double2* L, double2* Li, double* dg, StepShare& sh,
                       double tol) {
-  const int e = threadIdx.x & 255, h = threadIdx.x >> 8, i = e >> 4, j = e & 15;
-  double2 v = h ? make_double2(i == j ? 1.0 : 0.0, 0.0) : G[e];
+  const int e = threadIdx.x & 255, i = e >> 4, j = e & 15;
+  const bool on = threadIdx.x < 256;
+  double2 v = G[e], y = make_double2(i == j ? 1.0 : 0.0, 0.0);
   bool ok = true;
-  if (i == 0) sh.row[0][h][j] = v;
-  if (!h && j == 0) sh.col[0][i] = v;
+  if (on) {
+    if (i == 0) {
+      sh.row[0][0][j] = v;
+      sh.row[0][1][j] = y;
+    }
+    if (j == 0) sh.col[0][i] = v;
+  }
   __syncthreads();
 #pragma unroll
   for (int s = 0; s < BW; ++s) {
     const int cur = s & 1, nxt = cur ^ 1;
     const double p = sh.col[cur][s].x;
-    const double2 ci = sh.col[cur][i], rj = sh.row[cur][h][j];
+    const double2 ci = sh.col[cur][i];
     ok = ok && p > tol * G[s * BW + s].x;
-    if (i > s && (h || j > s)) v = csub(v, cmul(cscale(ci, fast_rcp(p)), rj));
+    if (on && i > s) {
+      const double2 l = cneg(cscale(ci, fast_rcp(p)));
+      if (j > s) v = cfma(l, sh.row[cur][0][j], v);
+      y = cfma(l, sh.row[cur][1][j], y);
+    }
     if (s + 1 < BW) {
-      if (i == s + 1) sh.row[nxt][h][j] = v;
-      if (!h && j == s + 1) sh.col[nxt][i] = v;
+      if (on) {
+        if (i == s + 1) {
+          sh.row[nxt][0][j] = v;
+          sh.row[nxt][1][j] = y;
+        }
+        if (j == s + 1) sh.col[nxt][i] = v;
+      }
       __syncthreads();
     }
   }
-  if (!h && i == j) dg[i] = fast_rsq(v.x);
+  if (on && i == j) dg[i] = fast_rsq(v.x);
   __syncthreads();
-  if (!h)
+  if (on) {
     L[i * LDT + j] = i >= j ? cscale(v, dg[j]) : czero();
-  else
-    Li[i * LDT + j] = i >= j ? cscale(v, dg[i]) : czero();
+    Li[i * LDT + j] = i >= j ? cscale(y, dg[i]) : czero();
+  }
   __syncthreads();
   return ok;
 }
@@ -266,13 +303,15 @@ BSE_DEV bool chol_inv(const double2* G, double2* L, double2* Li, double* dg, Ste
 // ------------------------------------------------------- panel, first pass
 // Q1 = P R1^-1 with R1 from the Gram matrix.  Panel state: 0 ok, 1 the Gram
 // matrix is not safely positive definite, 2 the panel is zero.
-__global__ __launch_bounds__(NT) void k_band_chol(BandArgs a, BandFirst f, int k) {
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_band_chol(BandArgs a, BandFirst f, int k) {
+  constexpr int RB = 16 * NW;
   const int pi = band_problem(f);
   const BandProb& p = a.p[pi];
   if (failed(p.info)) return;
   const int bx = (int)blockIdx.x - f.b[pi];
-  const int j0 = BW * k, t = j0 + BW, m = p.n - t, n = p.n;
-  __shared__ double2 red[NWV * 256];
+  const int j0 = BW * k, t = j0 + BW, n = p.n;
+  __shared__ double2 red[NW * 256];
   __shared__ double2 G[256], tmp[256], L[BW * LDT], Li[BW * LDT];
   __shared__ double dg[BW];
   __shared__ StepShare sh;
@@ -284,7 +323,7 @@ __global__ __launch_bounds__(NT) void k_band_chol(BandArgs a, BandFirst f, int k
   for (int c = 0; c < 4; ++c)
     pt[c] = p.M[min(row, n - 1) + (int64_t)(j0 + hi + 4 * c) * p.ld];
   // the partials come from k_band_w over rows j0 .. (t = 0: the first panel)
-  sum_partials(p.g1, cdiv(n - j0, RB), G, tmp);
+  sum_partials<NW>(p.g1, panel_blocks(n - j0), G, tmp);
   // every column zero: nothing to reflect
   bool zero = true;
 #pragma unroll
@@ -323,14 +362,120 @@ __global__ __launch_bounds__(NT) void k_band_chol(BandArgs a, BandFirst f, int k
   wave_lds_sync();
 #pragma unroll
   for (int c = 0; c < 4; ++c) g.mac(cconj(x[c]), x[c]);
-  reduce_tiles(g, red, p.g2 + (int64_t)bx * 256);
+  reduce_tiles<NW>(g, red, p.g2 + (int64_t)bx * 256);
 }
 
 // ------------------------------------------------ column-by-column panel
+// Panels of at most 64 rows, in registers of the block's first 256 threads:
+// thread (c, l) holds rows l + 16 q of column c, so a sum over rows is one over
+// the 16 lanes of a DPP row; one barrier per column.  xcol: 2 x 64 values, gv: 2 x
+// BW, Tl: BW x LDT (LDS).  Columns already reduced hold their reflector, whose
+// product with the new one gives T's next column.
+BSE_DEV void panel_small(const BandProb& p, int k, double2* xcol, double2* gv, double2* Tl) {
+  const int j0 = BW * k, t = j0 + BW, n = p.n, m = n - t;
+  const int tid = threadIdx.x, l = tid & 15, c = tid >> 4;
+  const bool on = tid < 256;
+  double2* V = v_of(p, k);
+  double2 a[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = l + 16 * q;
+    a[q] = keep2(on && r < m, p.M[min(t + r, n - 1) + (int64_t)(j0 + (c & 15)) * p.ld]);
+  }
+  if (on) Tl[c * LDT + l] = czero();
+  const int jn = min(BW, m);
+  double2 tprev = czero();
+  for (int j = 0; j <= jn; ++j) {
+    double2* xc = xcol + (j & 1) * 64;
+    if (on && c == j && j < jn) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xc[l + 16 * q] = a[q];
+    }
+    __syncthreads();
+    if (on && j > 0) {  // T[:i, i] = -tau_i T[:i, :i] (V^H v_i), i = j - 1
+      const int i = j - 1;
+      if (tid < i) {
+        double2 v = czero();
+        for (int q = tid; q < i; ++q) v = cfma(Tl[tid * LDT + q], gv[(i & 1) * BW + q], v);
+        Tl[tid * LDT + i] = cneg(cmul(tprev, v));
+      } else if (tid == i) {
+        Tl[i * LDT + i] = tprev;
+      }
+    }
+    if (j == jn) break;
+    double2 u[4];
+    double xn = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      u[q] = xc[l + 16 * q];
+      if (l + 16 * q > j) xn += cabs2(u[q]);
+    }
+    const double2 al = xc[j];
+    xn = row_sum(xn);
+    const double nn = cabs2(al) + xn;
+    double2 tau = czero(), scal = czero(), beta = al;
+    if (xn != 0.0 && nn > 1e-280) {
+      const double b = -copysign(sqrt(nn), al.x);
+      beta = make_double2(b, 0.0);
+      tau = make_double2((b - al.x) / b, -al.y / b);
+      const double2 dn = make_double2(al.x - b, al.y);
+      const double q = 1.0 / cabs2(dn);
+      scal = make_double2(dn.x * q, -dn.y * q);
+    }
+    double2 g = czero();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = l + 16 * q;
+      u[q] = r > j ? cmul(scal, u[q]) : make_double2(r == j ? 1.0 : 0.0, 0.0);
+      g = cfmac(u[q], a[q], g);
+    }
+    g = row_sum(g);
+    if (on && c > j) {
+      g = cneg(cmulc(tau, g));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[q] = cfma(u[q], g, a[q]);
+    } else if (on && c < j) {
+      if (l == 0) gv[(j & 1) * BW + c] = cconj(g);
+    } else if (on) {  // column j: R above and on the diagonal, then its reflector
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = l + 16 * q;
+        if (r <= j) p.M[t + r + (int64_t)(j0 + j) * p.ld] = r == j ? beta : a[q];
+        a[q] = u[q];
+      }
+    }
+    tprev = tau;
+  }
+  // columns past the last reflector (fewer rows than columns) hold R
+  if (on && c >= jn) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = l + 16 * q;
+      if (r < m) p.M[t + r + (int64_t)(j0 + c) * p.ld] = a[q];
+      a[q] = czero();
+    }
+  }
+  double2 d = czero();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = l + 16 * q;
+    if (on && r < m) {
+      V[(int64_t)(t + r) * BW + c] = a[q];
+      if (p.yp) d = cfmac(a[q], p.yp[t + r], d);
+    }
+  }
+  d = row_sum(d);
+  if (on && l == 0) p.pd[c] = d;
+  __syncthreads();
+  if (on) p.sm[tid] = Tl[c * LDT + l];
+}
+
 // Householder factorisation of P = S[t:, j0:j0+BW] by one block, in place
 // (row i <= column j of the result is R), V and T as the fast path leaves them.
-// sums: NWV * BW values, sv: 2 BW values (LDS); Tl: BW * LDT (LDS).
+// sums: NW * BW values, sv: BW values (LDS); Tl: BW * LDT (LDS).
+template <int NW>
 BSE_DEV void panel_direct(const BandProb& p, int k, double2* sums, double2* sv, double2* Tl) {
+  constexpr int NT = 64 * NW;
   const int j0 = BW * k, t = j0 + BW, n = p.n, m = n - t;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   double2* V = v_of(p, k);
@@ -346,7 +491,7 @@ BSE_DEV void panel_direct(const BandProb& p, int k, double2* sums, double2* sv, 
     __syncthreads();
     if (tid < BW) {
       double2 v = czero();
-      for (int w = 0; w < NWV; ++w) v = cadd(v, sums[w * BW + tid]);
+      for (int w = 0; w < NW; ++w) v = cadd(v, sums[w * BW + tid]);
       sv[tid] = v;
     }
     __syncthreads();
@@ -426,40 +571,140 @@ BSE_DEV void panel_direct(const BandProb& p, int k, double2* sums, double2* sv, 
       for (int c = 0; c < BW; ++c) s[c] = cadd(s[c], cmulc(V[(int64_t)(t + r) * BW + c], y));
     }
     block_sums(s);
-    const int nb = cdiv(m, RB);
+    const int nb = panel_blocks(m);
     for (int e = tid; e < nb * BW; e += NT) p.pd[e] = e < BW ? sv[e] : czero();
   }
 }
 
 // ------------------------------------------------------ panel, second pass
-__global__ __launch_bounds__(NT) void k_band_panel(BandArgs a, BandFirst f, int k) {
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_band_panel(BandArgs a, BandFirst f, int k) {
+  constexpr int RB = 16 * NW;
   const int pi = band_problem(f);
   const BandProb& p = a.p[pi];
   if (failed(p.info)) return;
   const int bx = (int)blockIdx.x - f.b[pi];
   const int j0 = BW * k, t = j0 + BW, n = p.n, m = n - t;
-  __shared__ double2 red[NWV * 256];
+  __shared__ double2 red[NW * 256];
   __shared__ double2 G[256], tmp[256], L[BW * LDT], Li[BW * LDT];
-  __shared__ double2 U[BW * LDT], Yi[BW * LDT], Dv[BW], ip[BW];
+  __shared__ double2 Dv[BW];
   __shared__ double dg[BW];
   __shared__ StepShare sh;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
   double2* V = v_of(p, k);
+  if (m < DIRECT_ROWS) {  // uniform; one block
+    panel_small(p, k, red, G, L);
+    return;
+  }
   const int row = t + bx * RB + wid * 16 + lo;
-  int state = m < DIRECT_ROWS ? 1 : p.ctl[0];  // uniform
+  const int e = tid & 255, i = e >> 4, j = e & 15;
+  const bool on = tid < 256;
+  int state = p.ctl[0];  // uniform
   double2 qf[4];
   if (state == 0) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) qf[c] = p.Q1[(int64_t)min(row, n - 1) * BW + hi + 4 * c];
-    sum_partials(p.g2, cdiv(m, RB), G, tmp);
-    // Q1 has to be near orthonormal for the second pass to end at rounding
-    bool near = true;
+    const double2 qt = p.Q1[(int64_t)(t + i) * BW + j];
+    sum_partials<NW>(p.g2, panel_blocks(m), G, tmp);
+    // R2 (in L) and its inverse (in Li), upper triangular, R2^H R2 = G = I + E.  For
+    // E below 1e-4 from the fixed point X = upper(E - X^H X) (diagonal halved) of R2
+    // = I + X, whose error goes from E^2 to E^3 and E^4, and 1 - X + X^2 - X^3:
+    // four products in place of sixteen dependent steps
+    const double2 E = csub(G[e], make_double2(i == j ? 1.0 : 0.0, 0.0));
+    const bool tiny = __syncthreads_and(fabs(E.x) < 1e-4 && fabs(E.y) < 1e-4);
+    if (tiny) {
+      const double half = i < j ? 1.0 : i == j ? 0.5 : 0.0;
+      double2 x = cscale(E, half);
+      for (int it = 0; it < 2; ++it) {
+        if (on) Li[i * LDT + j] = x;
+        __syncthreads();
+        double2 r = E;
 #pragma unroll
-    for (int s = 0; s < BW; ++s) near = near && fabs(G[s * BW + s].x - 1.0) < 0.1;
-    if (!chol_inv(G, L, Li, dg, sh, 0.5) || !near) state = 1;
+        for (int q = 0; q < BW; ++q) r = cfmac(cneg(Li[q * LDT + i]), Li[q * LDT + j], r);
+        x = cscale(r, half);
+        __syncthreads();
+      }
+      const double2 one = make_double2(i == j ? 1.0 : 0.0, 0.0);
+      double2 y = csub(one, x);
+      if (on) L[i * LDT + j] = cneg(x);
+      for (int it = 0; it < 2; ++it) {
+        if (on) Li[i * LDT + j] = y;
+        __syncthreads();
+        y = one;
+#pragma unroll
+        for (int q = 0; q < BW; ++q) y = cfma(L[i * LDT + q], Li[q * LDT + j], y);
+        __syncthreads();
+      }
+      if (on) {
+        L[i * LDT + j] = cadd(one, x);
+        Li[i * LDT + j] = y;
+      }
+    } else if (chol_inv(G, L, Li, dg, sh, 0.5)) {  // lower factors, transposed
+      const double2 l = cconj(L[j * LDT + i]), li = cconj(Li[j * LDT + i]);
+      __syncthreads();
+      if (on) {
+        L[i * LDT + j] = l;
+        Li[i * LDT + j] = li;
+      }
+    } else {
+      state = 1;
+    }
+    if (on) tmp[e] = qt;
+    __syncthreads();
+  }
+  double2 y = make_double2(i == j ? 1.0 : 0.0, 0.0);
+  if (state == 0) {
+    // ---- (Q_top - D)^-1, Q_top = Q1[:16] R2^-1, by Gauss-Jordan elimination beside
+    // the identity (one element of each per thread, one barrier per column); D_s
+    // opposes the pivot's phase, so that no pivot is below 1
+    double2 v = czero();
+#pragma unroll
+    for (int q = 0; q < BW; ++q) v = cfma(tmp[i * BW + q], Li[q * LDT + j], v);
+    if (on) {
+      if (i == 0) {
+        sh.row[0][0][j] = v;
+        sh.row[0][1][j] = y;
+      }
+      if (j == 0) sh.col[0][i] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < BW; ++s) {
+      const int cur = s & 1, nxt = cur ^ 1;
+      const double2 pv = sh.col[cur][s], ci = sh.col[cur][i];
+      const double2 rv = sh.row[cur][0][j], ry = sh.row[cur][1][j];
+      const double a2 = cabs2(pv);
+      double2 D = make_double2(-1.0, 0.0), inv = make_double2(1.0, 0.0);
+      if (a2 > 1e-290) {
+        const double ra = fast_rsq(a2), ab = a2 * ra;
+        D = make_double2(-pv.x * ra, -pv.y * ra);
+        inv = cscale(cconj(pv), ra * fast_rcp(ab + 1.0));  // 1 / (pv - D)
+      }
+      if (i == s) {
+        v = cmul(rv, inv);
+        y = cmul(ry, inv);
+        if (on && j == s) Dv[s] = D;
+      } else {
+        const double2 l = cneg(cmul(ci, inv));
+        v = cfma(l, rv, v);
+        y = cfma(l, ry, y);
+      }
+      if (s + 1 < BW) {
+        if (on) {
+          if (i == s + 1) {
+            sh.row[nxt][0][j] = v;
+            sh.row[nxt][1][j] = y;
+          }
+          if (j == s + 1) sh.col[nxt][i] = v;
+        }
+        __syncthreads();
+      }
+    }
+    // an inverse far above the order of 1 would cost H its unitarity
+    if (!__syncthreads_and(fabs(y.x) < 1e3 && fabs(y.y) < 1e3)) state = 1;
   }
   if (state == 1) {
-    if (bx == 0) panel_direct(p, k, red, G, L);
+    if (bx == 0) panel_direct<NW>(p, k, red, G, L);
     return;
   }
   if (state == 2) {  // H = I
@@ -468,111 +713,37 @@ __global__ __launch_bounds__(NT) void k_band_panel(BandArgs a, BandFirst f, int 
       for (int r = 0; r < 4; ++r) V[(int64_t)row * BW + hi + 4 * r] = czero();
     }
     if (tid < BW) p.pd[(int64_t)bx * BW + tid] = czero();
-    if (bx == 0 && tid < 256) p.sm[tid] = czero();
+    if (bx == 0 && on) p.sm[tid] = czero();
     return;
   }
-
-  // ---- Q_top = Q1[:16] R2^-1, then LU of Q_top - D beside the identity
-  const int e = tid & 255, h = tid >> 8, i = e >> 4, j = e & 15;
-  if (!h) tmp[e] = p.Q1[(int64_t)(t + i) * BW + j];
-  __syncthreads();
-  double2 v = make_double2(h && i == j ? 1.0 : 0.0, 0.0);
-  if (!h) {
-#pragma unroll
-    for (int q = 0; q < BW; ++q)  // sum_q Q1[i][q] conj(Li[j][q])
-      v = cadd(v, cmulc(Li[j * LDT + q], tmp[i * BW + q]));
-  }
-  if (i == 0) sh.row[0][h][j] = v;
-  if (!h && j == 0) sh.col[0][i] = v;
-  __syncthreads();
-#pragma unroll
-  for (int s = 0; s < BW; ++s) {
-    const int cur = s & 1, nxt = cur ^ 1;
-    const double2 pv = sh.col[cur][s];
-    const double2 ci = sh.col[cur][i], rj = sh.row[cur][h][j];
-    const double a2 = cabs2(pv);
-    double2 D = make_double2(-1.0, 0.0), piv = make_double2(1.0, 0.0), inv = piv;
-    if (a2 > 1e-290) {
-      const double ra = fast_rsq(a2), ab = a2 * ra;
-      D = make_double2(-pv.x * ra, -pv.y * ra);
-      piv = csub(pv, D);                               // p (1 + 1/|p|)
-      inv = cscale(cconj(pv), ra * fast_rcp(ab + 1.0));  // 1 / piv
-    }
-    if (i > s) {
-      const double2 li = cmul(ci, inv);
-      if (h || j > s) v = csub(v, cmul(li, rj));
-      if (!h && j == s) v = li;
-    }
-    if (!h && i == s && j == s) {
-      v = piv;
-      Dv[s] = D;
-      ip[s] = inv;
-    }
-    if (s + 1 < BW) {
-      if (i == s + 1) sh.row[nxt][h][j] = v;
-      if (!h && j == s + 1) sh.col[nxt][i] = v;
-      __syncthreads();
-    }
-  }
-  if (!h)
-    U[i * LDT + j] = v;   // U' on and above the diagonal, V_top below it
-  else
-    Yi[i * LDT + j] = v;  // V_top^-1
-  __syncthreads();
-  // ---- X = U'^-1 by backward substitution (threads 0..255, one row per step)
-  double2 x = make_double2(i == j ? 1.0 : 0.0, 0.0);
-  if (!h && i == BW - 1) sh.row[0][0][j] = x = cmul(x, ip[BW - 1]);
-  __syncthreads();
-#pragma unroll
-  for (int s = BW - 1; s > 0; --s) {
-    const int cur = (BW - 1 - s) & 1, nxt = cur ^ 1;
-    if (!h && i < s) {
-      x = csub(x, cmul(U[i * LDT + s], sh.row[cur][0][j]));
-      if (i == s - 1) sh.row[nxt][0][j] = x = cmul(x, ip[s - 1]);
-    }
-    __syncthreads();
-  }
-  if (!h) G[e] = x;
-  __syncthreads();
-  // Mm = R2^-1 U'^-1 (in tmp); T = -U' D^* V_top^-H and R = D R2 R1 by block 0
-  if (!h) {
-    double2 s = czero();
-#pragma unroll
-    for (int q = 0; q < BW; ++q) s = cadd(s, cmulc(Li[q * LDT + i], G[q * BW + j]));
-    tmp[e] = s;
-  } else if (bx == 0) {
-    double2 s = czero(), r = czero();
-#pragma unroll
-    for (int q = 0; q < BW; ++q)
-      if (q >= i) s = csub(s, cmul(cmulc(Dv[q], U[i * LDT + q]), cconj(Yi[j * LDT + q])));
-    p.sm[e] = s;
+  if (bx == 0 && on) {  // T = -D^* (Q_top - D)^-H and R = D R2 R1
+    p.sm[j * BW + i] = cneg(cconj(cmul(Dv[j], y)));
     if (i <= j) {
-      for (int q = i; q <= j; ++q)
-        r = cadd(r, cmul(cconj(L[q * LDT + i]), cconj(p.sm[256 + j * BW + q])));
+      double2 r = czero();
+      for (int q = i; q <= j; ++q) r = cfmac(p.sm[256 + j * BW + q], L[i * LDT + q], r);
       p.M[t + i + (int64_t)(j0 + j) * p.ld] = cmul(Dv[i], r);
     }
   }
-  __syncthreads();
-  Acc acc;
+  Acc acc;  // V = Q1 R2^-1 - [D; 0]
 #pragma unroll
   for (int c = 0; c < 4; ++c)
-    acc.mac(tmp[(hi + 4 * c) * BW + lo], keep2(row < n, qf[c]));
+    acc.mac(Li[(hi + 4 * c) * LDT + lo], keep2(row < n, qf[c]));
   const bool top = bx == 0 && wid == 0;
-  const double2 y = p.yp ? p.yp[min(row, n - 1)] : czero();
+  const double2 yr = p.yp ? p.yp[min(row, n - 1)] : czero();
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int vec = hi + 4 * r;
     double2 o = acc.at(r);
-    if (top) o = lo == vec ? make_double2(1.0, 0.0) : keep2(lo > vec, U[lo * LDT + vec]);
+    if (top && lo == vec) o = csub(o, Dv[vec]);
     if (row < n) V[(int64_t)row * BW + vec] = o;
-    const double2 d = row_sum(keep2(row < n, cmulc(o, y)));
+    const double2 d = row_sum(keep2(row < n, cmulc(o, yr)));
     if (lo == 0) red[wid * BW + vec] = d;
   }
   __syncthreads();
   if (tid < BW) {
     double2 s = czero();
 #pragma unroll
-    for (int w = 0; w < NWV; ++w) s = cadd(s, red[w * BW + tid]);
+    for (int w = 0; w < NW; ++w) s = cadd(s, red[w * BW + tid]);
     p.pd[(int64_t)bx * BW + tid] = s;
   }
 }
@@ -588,16 +759,18 @@ __host__ __device__ inline int block_of(int64_t T, int G, int64_t t) {
   return (int)(((t + 1) * G - 1) / T);
 }
 
-constexpr int STEP_THREADS = 256;  // wavefront w: tile columns 16 w .. 16 w + 15
-constexpr int SR = ST / 16;        // 16-row blocks of a tile
-
+template <int ST>
 struct StepSmem {
   double2 v[ST][LDT], w[ST][LDT];  // previous panel's V and W, the tile-row's rows
   double2 x[ST][LDT];              // this panel's V
-  double2 tr[4][16 * LDT];         // per wavefront: a 16 x 16 block, transposed
+  double2 tr[ST / 16][16 * LDT];   // per wavefront: a 16 x 16 block, transposed
 };
 
-__global__ __launch_bounds__(STEP_THREADS) void k_band_step(BandArgs a, BandFirst f, int k) {
+// Wavefront w of a block: tile columns 16 w .. 16 w + 15.
+template <int ST>
+__global__ __launch_bounds__(4 * ST, 2) void k_band_step(BandArgs a, BandFirst f, int k) {
+  constexpr int SR = ST / 16;              // 16-row blocks of a tile, wavefronts of a block
+  constexpr int STEP_THREADS = 64 * SR;
   const int pi = band_problem(f);
   const BandProb& p = a.p[pi];
   if (failed(p.info)) return;
@@ -605,7 +778,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_band_step(BandArgs a, BandFirs
   const int t = BW * (k + 1), n = p.n, nI = cdiv(n - t, ST);
   const int64_t T = (int64_t)nI * (nI + 1) / 2, N16 = (int64_t)n * BW, ld = p.ld;
   const int64_t t_end = run_start(T, G, bx + 1);
-  __shared__ StepSmem sm;
+  __shared__ StepSmem<ST> sm;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
   const bool upd = k > 0;  // a previous panel to apply
   const double2* __restrict__ Vn = v_of(p, k);
@@ -722,8 +895,8 @@ __global__ __launch_bounds__(STEP_THREADS) void k_band_step(BandArgs a, BandFirs
     if (J == I || !more) {
       // end of a piece: the wavefronts' row sums, two 16-row blocks at a time
       // through the operand rows' space
-      double2* red = &sm.v[0][0];  // 4 x 2 x 256 values of the 3 ST LDT there are
-      static_assert(4 * 2 * 256 <= 3 * ST * LDT, "row sums fit in the operand rows");
+      double2* red = &sm.v[0][0];  // SR x 2 x 256 values of the 3 ST LDT there are
+      static_assert(SR * 2 * 256 <= 3 * ST * LDT, "row sums fit in the operand rows");
       const int slot = bx - block_of(T, G, (int64_t)I * (I + 1) / 2);
       double2* y = Y + (int64_t)slot * N16;
 #pragma unroll
@@ -739,7 +912,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_band_step(BandArgs a, BandFirs
           const int row = t + I * ST + half * 32 + (e >> 4);
           double2 o = czero();
 #pragma unroll
-          for (int w = 0; w < 4; ++w) o = cadd(o, red[w * 512 + e]);
+          for (int w = 0; w < SR; ++w) o = cadd(o, red[w * 512 + e]);
           if (row < n) y[(int64_t)row * BW + (e & 15)] = o;
         }
       }
@@ -760,49 +933,75 @@ __global__ __launch_bounds__(STEP_THREADS) void k_band_step(BandArgs a, BandFirs
 }
 
 // --------------------------------------------------- X, V^H X and the probe
-__global__ __launch_bounds__(NT) void k_band_x(BandArgs a, BandFirst f, int k, BandFirst gs) {
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_band_x(BandArgs a, BandFirst f, int k, BandFirst gs) {
+  constexpr int RB = 16 * NW, NT = 64 * NW;
   const int pi = band_problem(f);
   const BandProb& p = a.p[pi];
   if (failed(p.info)) return;
   const int bx = (int)blockIdx.x - f.b[pi];
-  const int t = BW * (k + 1), n = p.n, m = n - t, nI = cdiv(m, ST);
+  const int t = BW * (k + 1), n = p.n, m = n - t, ST = step_tile(m), nI = cdiv(m, ST);
   const int G = gs.b[pi];  // blocks of this problem's k_band_step launch
   const int64_t T = (int64_t)nI * (nI + 1) / 2, N16 = (int64_t)n * BW;
   __shared__ double2 xs[RB * LDT];
-  __shared__ double2 red[NWV * 256];
-  __shared__ double2 sc[BW];
+  __shared__ double2 red[NW * 256];
+  __shared__ double2 sc[BW], cv[BW], Ts[256];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
   const double2* V = v_of(p, k);
-  // the sums over the slots, four values per thread
-#pragma unroll
-  for (int q = 0; q < RB * BW / NT; ++q) {
-    const int e = tid + q * NT, rr = e >> 4, c = e & 15, lr = bx * RB + rr;
-    double2 x = czero();
-    if (lr < m) {
-      const int Ir = lr / ST;
-      const int64_t s0 = (int64_t)Ir * (Ir + 1) / 2;
-      const int nrs = block_of(T, G, s0 + Ir) - block_of(T, G, s0) + 1;
-      const int tot = nrs + nI - Ir;
-      const double2* y = p.Y + (int64_t)(t + lr) * BW + c;
-      auto at = [&](int u) { return y + (int64_t)(u < nrs ? u : p.ycs + Ir + u - nrs) * N16; };
-      int u = 0;
-      for (; u + 8 <= tot; u += 8) {
-        double2 v[8];
-#pragma unroll
-        for (int w = 0; w < 8; ++w) v[w] = *at(u + w);
-#pragma unroll
-        for (int w = 0; w < 8; ++w) x = cadd(x, v[w]);
-      }
-      for (; u < tot; ++u) x = cadd(x, *at(u));
-      p.X[(int64_t)(t + lr) * BW + c] = x;
-    }
-    xs[rr * LDT + c] = x;
-  }
-  if (p.yp) {  // sum of the blocks' V^H y
-    const int c = tid & 15, g = tid >> 4;  // 32 groups
+  if (p.yp) {
+    if (tid < 256) Ts[tid] = p.sm[tid];
+    const int c = tid & 15, g = tid >> 4;  // partial sums of the blocks' V^H y
     double2 s = czero();
-    for (int b = g; b < cdiv(m, RB); b += NT / BW) s = cadd(s, p.pd[(int64_t)b * BW + c]);
+    for (int b = g; b < panel_blocks(m); b += NT / BW) s = cadd(s, p.pd[(int64_t)b * BW + c]);
     red[g * BW + c] = s;
+  }
+  double2 vf[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    vf[c] = V[(int64_t)min(t + bx * RB + wid * 16 + hi + 4 * c, n - 1) * BW + lo];
+  // the sums over the slots: column c of rows rr0 + 16 w, ST rows of a tile-row at
+  // a time (four rows per thread, eight slots of each in flight)
+  {
+    const int c = tid & 15, rr0 = tid >> 4;
+    constexpr int RT = NT / BW;      // rows per pass
+    constexpr int QR = RB / RT;      // passes
+    static_assert(QR == 4 && RT * 4 == RB, "four rows per thread");
+    double2 x[QR];
+    int nrs[QR], tot[QR], Ir[QR], lr[QR], most = 0;
+#pragma unroll
+    for (int q = 0; q < QR; ++q) {
+      x[q] = czero();
+      lr[q] = min(bx * RB + rr0 + RT * q, m - 1);
+      Ir[q] = lr[q] / ST;
+      const int64_t s0 = (int64_t)Ir[q] * (Ir[q] + 1) / 2;
+      nrs[q] = block_of(T, G, s0 + Ir[q]) - block_of(T, G, s0) + 1;
+      tot[q] = nrs[q] + nI - Ir[q];
+      most = max(most, tot[q]);
+    }
+    const double2* __restrict__ Y = p.Y + (int64_t)t * BW + c;
+    for (int u0 = 0; u0 < most; u0 += 8) {
+      double2 v[QR][8];
+#pragma unroll
+      for (int q = 0; q < QR; ++q)
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+          const int u = min(u0 + w, tot[q] - 1);
+          v[q][w] = Y[(int64_t)(u < nrs[q] ? u : p.ycs + Ir[q] + u - nrs[q]) * N16 +
+                      (int64_t)lr[q] * BW];
+        }
+#pragma unroll
+      for (int q = 0; q < QR; ++q)
+#pragma unroll
+        for (int w = 0; w < 8; ++w)
+          if (u0 + w < tot[q]) x[q] = cadd(x[q], v[q][w]);
+    }
+#pragma unroll
+    for (int q = 0; q < QR; ++q) {
+      const int rr = rr0 + RT * q;
+      const bool in = bx * RB + rr < m;
+      if (in) p.X[(int64_t)(t + bx * RB + rr) * BW + c] = x[q];
+      xs[rr * LDT + c] = keep2(in, x[q]);
+    }
   }
   __syncthreads();
   if (p.yp && tid < BW) {
@@ -813,34 +1012,43 @@ __global__ __launch_bounds__(NT) void k_band_x(BandArgs a, BandFirst f, int k, B
   Acc z;
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    const int rr = wid * 16 + hi + 4 * c, row = t + bx * RB + rr;
-    z.mac(keep2(row < n, cconj(V[(int64_t)min(row, n - 1) * BW + lo])), xs[rr * LDT + lo]);
+    const int rr = wid * 16 + hi + 4 * c;
+    z.mac(keep2(t + bx * RB + rr < n, cconj(vf[c])), xs[rr * LDT + lo]);
   }
   __syncthreads();
-  reduce_tiles(z, red, p.z + (int64_t)bx * 256);
-  if (p.yp && tid < RB && bx * RB + tid < m) {
-    // y -= V (T^H (V^H y))
-    const int row = t + bx * RB + tid;
+  if (p.yp && tid < BW) {  // T^H (V^H y)
+    double2 s = czero();
+    for (int i = 0; i < BW; ++i) s = cfmac(Ts[i * BW + tid], sc[i], s);
+    cv[tid] = s;
+  }
+  reduce_tiles<NW>(z, red, p.z + (int64_t)bx * 256);
+  if (p.yp) {  // y -= V (T^H (V^H y)), four threads per row
+    const int row = t + bx * RB + (tid >> 2), c0 = 4 * (tid & 3);
     double2 d = czero();
-    for (int j = 0; j < BW; ++j) {
-      double2 cj = czero();
-      for (int i = 0; i <= j; ++i) cj = cadd(cj, cmulc(p.sm[i * BW + j], sc[i]));
-      d = cadd(d, cmul(V[(int64_t)row * BW + j], cj));
+    if (row < n) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) d = cfma(V[(int64_t)row * BW + c0 + q], cv[c0 + q], d);
     }
-    p.yp[row] = csub(p.yp[row], d);
+    d.x += dpp_mov<0xB1>(d.x);
+    d.y += dpp_mov<0xB1>(d.y);
+    d.x += dpp_mov<0x4E>(d.x);
+    d.y += dpp_mov<0x4E>(d.y);
+    if (row < n && c0 == 0) p.yp[row] = csub(p.yp[row], d);
   }
 }
 
 // ------------------------------------- W, the next panel's columns, its Gram
 // k < 0: nothing to apply, the Gram partials of the first panel.
-__global__ __launch_bounds__(NT) void k_band_w(BandArgs a, BandFirst f, int k) {
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_band_w(BandArgs a, BandFirst f, int k) {
+  constexpr int RB = 16 * NW;
   const int pi = band_problem(f);
   const BandProb& p = a.p[pi];
   if (failed(p.info)) return;
   const int bx = (int)blockIdx.x - f.b[pi];
   const int t = BW * (k + 1), n = p.n, m = n - t;
-  __shared__ double2 red[NWV * 256];
-  __shared__ double2 Z[256], tmp[256], Ts[256];
+  __shared__ double2 red[NW * 256];
+  __shared__ double2 Z[256], tmp[256], Ts[256], Xt[256], Vt[256], Wc[BW * LDT];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
   const int row = t + bx * RB + wid * 16 + lo;
   double2 s[4];  // the next panel's columns t .. t + 15 on this row (transposed block)
@@ -850,47 +1058,58 @@ __global__ __launch_bounds__(NT) void k_band_w(BandArgs a, BandFirst f, int k) {
   if (k >= 0) {
     const double2* V = v_of(p, k);
     double2* W = w_of(p, k);
-    double2 xf[4], vf[4], xc[4], vc[4];  // rows of X and V: this tile's, the top tile's
-    const int rt = min(t + lo, n - 1);
+    double2 xf[4], vf[4];  // this tile's rows of X and V
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const int64_t at = (int64_t)min(row, n - 1) * BW + hi + 4 * c, ac = (int64_t)rt * BW + hi + 4 * c;
+      const int64_t at = (int64_t)min(row, n - 1) * BW + hi + 4 * c;
       xf[c] = keep2(row < n, p.X[at]);
       vf[c] = keep2(row < n, V[at]);
-      xc[c] = keep2(t + lo < n, p.X[ac]);
-      vc[c] = keep2(t + lo < n, V[ac]);
     }
-    if (tid < 256) Ts[tid] = p.sm[tid];
-    sum_partials(p.z, cdiv(m, RB), Z, tmp);
-    Acc zt, nn;  // Z T, T^H (Z T)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) zt.mac(Z[lo * BW + hi + 4 * c], Ts[(hi + 4 * c) * BW + lo]);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) nn.mac(cconj(Ts[(hi + 4 * c) * BW + lo]), zt.at(c));
-    double2 nh[4], tt[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      nh[c] = cscale(nn.at(c), -0.5);  // A operand of -1/2 (T^H Z T)^T
-      tt[c] = Ts[(hi + 4 * c) * BW + lo];  // A operand of T^T
+    const int e = tid & 255, i = e >> 4, j = e & 15;
+    if (tid < 256) {
+      const int64_t at = (int64_t)min(t + i, n - 1) * BW + j;
+      Ts[e] = p.sm[e];
+      Xt[e] = keep2(t + i < n, p.X[at]);
+      Vt[e] = keep2(t + i < n, V[at]);
     }
-    Acc wt, wc;  // W^T of this tile and of the top tile
+    sum_partials<NW>(p.z, panel_blocks(m), Z, tmp);
+    // Z T and X_top T, then N = -1/2 T^H (Z T), then W_top = X_top T + V_top N: one
+    // element per thread on the vector ALU (chains of 16; the matrix cores would
+    // take twelve dependent products for each)
+    double2 zt = czero(), xt = czero(), nn = czero();
+    if (tid < 256) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      wt.mac(tt[c], xf[c]);
-      wc.mac(tt[c], xc[c]);
+      for (int q = 0; q < BW; ++q) {
+        zt = cfma(Z[i * BW + q], Ts[q * BW + j], zt);
+        xt = cfma(Xt[i * BW + q], Ts[q * BW + j], xt);
+      }
+      tmp[e] = zt;
     }
+    __syncthreads();
+    if (tid < 256) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      wt.mac(nh[c], vf[c]);
-      wc.mac(nh[c], vc[c]);
+      for (int q = 0; q < BW; ++q) nn = cfmac(Ts[q * BW + i], tmp[q * BW + j], nn);
+      Z[e] = cscale(nn, -0.5);
     }
+    __syncthreads();
+    if (tid < 256) {
+#pragma unroll
+      for (int q = 0; q < BW; ++q) xt = cfma(Vt[i * BW + q], Z[q * BW + j], xt);
+      Wc[i * LDT + j] = xt;
+    }
+    Acc wt;  // W^T of this tile
+#pragma unroll
+    for (int c = 0; c < 4; ++c) wt.mac(Ts[(hi + 4 * c) * BW + lo], xf[c]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) wt.mac(Z[(hi + 4 * c) * BW + lo], vf[c]);
+    __syncthreads();
     Acc u;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const double2 wr = wt.at(r);
       if (row < n) W[(int64_t)row * BW + hi + 4 * r] = wr;
-      u.mac(cconj(wc.at(r)), vf[r]);
-      u.mac(cconj(vc[r]), wr);
+      u.mac(cconj(Wc[lo * LDT + hi + 4 * r]), vf[r]);
+      u.mac(cconj(Vt[lo * BW + hi + 4 * r]), wr);
     }
     // lower triangle only in the top tile, its diagonal real
     const bool top = bx == 0 && wid == 0;
@@ -923,7 +1142,7 @@ __global__ __launch_bounds__(NT) void k_band_w(BandArgs a, BandFirst f, int k) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) g.mac(cconj(x[c]), x[c]);
   }
-  reduce_tiles(g, red, p.g1 + (int64_t)bx * 256);
+  reduce_tiles<NW>(g, red, p.g1 + (int64_t)bx * 256);
 }
 
 // ------------------------------------------------------------ band storage
@@ -1322,10 +1541,17 @@ int device_cus() {
 // The control words in complex elements, rounded to 256 bytes.
 int64_t ctl_elems(int64_t n) { return (((int64_t)band_ctl_ints((int)n) + 63) / 64) * 16; }
 
-// Blocks of a k_band_step launch over a trailing matrix of order m.
+// Blocks of a k_band_step launch over a trailing matrix of order m: up to eight
+// wavefronts per compute unit, two per SIMD.
 int step_grid(int64_t m) {
-  const int64_t nI = (m + ST - 1) / ST, T = nI * (nI + 1) / 2;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(2 * device_cus(), T));
+  const int64_t st = step_tile(m), nI = (m + st - 1) / st, T = nI * (nI + 1) / 2;
+  return (int)std::max<int64_t>(1, std::min<int64_t>((128 / st) * device_cus(), T));
+}
+
+// Slots of k_band_step's partial products: two per tile-row, for the largest order
+// of each tile edge.
+int64_t step_slots(int64_t n) {
+  return 2 * std::max((n + 63) / 64, (std::min<int64_t>(n, STEP_SMALL) + 31) / 32);
 }
 
 }  // namespace
@@ -1337,12 +1563,12 @@ bool tridiagonalise_band(const BandItem* it_all, int np_all, hipStream_t s) {
     BandArgs A{};
     int64_t nmax = 0;
     for (int q = 0; q < np; ++q) {
-      const int64_t n = it[q].n, nb = (n + RB - 1) / RB;
+      const int64_t n = it[q].n, nb = (n + 63) / 64;
       BandProb& p = A.p[q];
       p.M = it[q].M;
       p.ld = it[q].ld;
       p.n = (int)n;
-      p.ycs = (int)((n + ST - 1) / ST);
+      p.ycs = (int)(step_slots(n) / 2);
       p.VW = it[q].b.VW;
       p.Q1 = it[q].b.q1x;
       p.X = p.Q1 + n * BW;
@@ -1371,25 +1597,45 @@ bool tridiagonalise_band(const BandItem* it_all, int np_all, hipStream_t s) {
       f.b[BAND_BATCH_MAX] = tot;
       return f;
     };
-    const BandFirst f0 = ranges([&](int64_t n) { return n > BW ? cdiv(n, RB) : 0; });
-    if (f0.b[BAND_BATCH_MAX] > 0)
-      BSE_LAUNCH(k_band_w, dim3(f0.b[BAND_BATCH_MAX]), dim3(NT), 0, s, A, f0, -1);
+    // the panel kernels, in one launch per block size for the problems whose
+    // trailing order asks for it
+    auto panel = [&](int t, int least, auto launch) {
+      for (int rows : {64, 128}) {
+        const BandFirst f = ranges([&](int64_t n) {
+          return n - t >= least && panel_rows(n - t) == rows ? panel_blocks(n - t) : 0;
+        });
+        if (f.b[BAND_BATCH_MAX] > 0) launch(rows, f, dim3(f.b[BAND_BATCH_MAX]));
+      }
+    };
+#define BAND_LAUNCH(name, least, ...)                                                        \
+  panel(t, least, [&](int rows, const BandFirst& f, dim3 grid) {                              \
+    if (rows == 64)                                                                          \
+      BSE_LAUNCH(name<4>, grid, dim3(256), 0, s, A, f, __VA_ARGS__);                          \
+    else                                                                                     \
+      BSE_LAUNCH(name<8>, grid, dim3(512), 0, s, A, f, __VA_ARGS__);                          \
+  })
+    int t = 0;  // first row and column of the trailing matrix
+    BAND_LAUNCH(k_band_w, BW + 1, -1);
     for (int k = 0; BW * (k + 1) < nmax; ++k) {
-      auto order = [&](int64_t n) { return n - BW * (k + 1); };  // trailing order
-      const BandFirst fr = ranges([&](int64_t n) { return order(n) > 0 ? cdiv(order(n), RB) : 0; });
-      const BandFirst fc = ranges(
-          [&](int64_t n) { return order(n) >= DIRECT_ROWS ? cdiv(order(n), RB) : 0; });
-      const BandFirst fs = ranges([&](int64_t n) { return order(n) > 0 ? step_grid(order(n)) : 0; });
-      BandFirst gs{};
-      for (int q = 0; q < np; ++q) gs.b[q] = fs.b[q + 1] - fs.b[q];
-      const dim3 rows(fr.b[BAND_BATCH_MAX]);
-      if (fc.b[BAND_BATCH_MAX] > 0)
-        BSE_LAUNCH(k_band_chol, dim3(fc.b[BAND_BATCH_MAX]), dim3(NT), 0, s, A, fc, k);
-      BSE_LAUNCH(k_band_panel, rows, dim3(NT), 0, s, A, fr, k);
-      BSE_LAUNCH(k_band_step, dim3(fs.b[BAND_BATCH_MAX]), dim3(STEP_THREADS), 0, s, A, fs, k);
-      BSE_LAUNCH(k_band_x, rows, dim3(NT), 0, s, A, fr, k, gs);
-      BSE_LAUNCH(k_band_w, rows, dim3(NT), 0, s, A, fr, k);
+      t = BW * (k + 1);
+      BandFirst gs{};  // blocks of each problem's k_band_step launch
+      for (int q = 0; q < np; ++q) gs.b[q] = A.p[q].n > t ? step_grid(A.p[q].n - t) : 0;
+      BAND_LAUNCH(k_band_chol, DIRECT_ROWS, k);
+      BAND_LAUNCH(k_band_panel, 1, k);
+      for (int st : {32, 64}) {
+        const BandFirst fs = ranges(
+            [&](int64_t n) { return n > t && step_tile(n - t) == st ? step_grid(n - t) : 0; });
+        const dim3 grid(fs.b[BAND_BATCH_MAX]);
+        if (grid.x == 0) continue;
+        if (st == 32)
+          BSE_LAUNCH(k_band_step<32>, grid, dim3(128), 0, s, A, fs, k);
+        else
+          BSE_LAUNCH(k_band_step<64>, grid, dim3(256), 0, s, A, fs, k);
+      }
+      BAND_LAUNCH(k_band_x, 1, k, gs);
+      BAND_LAUNCH(k_band_w, 1, k);
     }
+#undef BAND_LAUNCH
     const BandFirst fp = ranges([&](int64_t n) { return (int)std::min<int64_t>(cdiv(n * ABS, 256), 1024); });
     BSE_LAUNCH(k_band_pack, dim3(fp.b[BAND_BATCH_MAX]), dim3(256), 0, s, A, fp);
     // sweeps in flight: one group per 2 CS BW columns of the band, with room
@@ -1403,9 +1649,9 @@ bool tridiagonalise_band(const BandItem* it_all, int np_all, hipStream_t s) {
 }
 
 int64_t band_big_bytes(int64_t n) {
-  const int64_t slots = n > BW ? 2 * ((n + ST - 1) / ST) * n * BW : 0;
+  const int64_t slots = n > BW ? step_slots(n) * n * BW : 0;
   return 16 * (band_elems(n) + ctl_elems(n) + slots);
 }
 int64_t band_part_bytes(int64_t n) {
-  return 16 * (((n + RB - 1) / RB) * (3 * 256 + BW) + 512);
+  return 16 * (((n + 63) / 64) * (3 * 256 + BW) + 512);
 }
