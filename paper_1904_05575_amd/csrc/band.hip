@@ -1213,17 +1213,12 @@ constexpr int BUFFER_FLAGS = 0x00027000;  // raw buffer, 32-bit data
 // One task of a sweep takes two wavefronts: one works on the block below the
 // diagonal and forms the reflector, the other applies the reflector to the
 // diagonal block and the probe one step later (what the next sweep needs of them
-// is then still one step ahead of its use).  The kernel is bound by the
-// instructions its four SIMDs issue per step, so the products with vectors run
-// on the vector ALU (four values per lane, then sums over the lane groups) and
-// the rank-two updates on the matrix cores, which take the vectors at index
-// lo = l % 16 as they are: a 16 x 16 x 4 product holds both complex outer products
-// of an update, one for its real and one for its imaginary part.  Blocks that are
-// updated are held as the matrix cores return them: register r of lane l the
-// element at row hi + 4 r, hi = l / 16, and column lo.
-BSE_DEV double pick4(int hi, double a, double b, double c, double d) {
-  return hi < 2 ? (hi == 0 ? a : b) : (hi == 2 ? c : d);
-}
+// is then still one step ahead of its use).  The kernel is bound by what its four
+// SIMDs issue per step.  Lane l: lo = l % 16, hi = l / 16.  Blocks that are updated
+// are held with column lo and rows hi + 4 c, so that sums over rows run over the
+// lane's four values and the four lane groups.  (The rank-two updates on the matrix
+// cores, a 16 x 16 x 4 product each for the real and the imaginary part, take more
+// instructions to arrange than the vector ALU's 32.)
 
 // The block at rows r0 .. r0 + 15 and columns r0 - 16 .. r0 - 1 (first: the column
 // s alone), by one wavefront: the previous reflector from the right, B - z v^H; the
@@ -1237,20 +1232,20 @@ BSE_DEV double chase_bulge(double2* ring, double2* ub, int lo, int hi, int r0, b
                            double2 x, double2& v, double2 (&vq)[4], double2& tau) {
   // element (i, j) of the block is diagonal BW + i - j of column r0 - BW + j
   auto at = [&](int i, int j) { return ((r0 - BW + j) & (RING - 1)) * ABS + BW + i - j; };
-  double2 Bt[4], xq[4], z = czero(), b0 = czero();
+  double2 Bt[4], xq[4], zq[4], b0 = czero();
   if (!first) {  // uniform
-    double2 z0 = czero(), z1 = czero(), B[4];
+    double2 B[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) B[c] = ring[at(lo, hi + 4 * c)];
 #pragma unroll
     for (int c = 0; c < 4; ++c) Bt[c] = ring[at(hi + 4 * c, lo)];
     b0 = ring[at(0, lo)];
-    z0 = cfma(B[0], vq[0], z0);
-    z1 = cfma(B[1], vq[1], z1);
-    z0 = cfma(B[2], vq[2], z0);
-    z1 = cfma(B[3], vq[3], z1);
-    z = cmul(tau, quad_rows_sum(cadd(z0, z1)));
-    x = csub(x, z);  // the reflector's first element is 1
+#pragma unroll
+    for (int c = 0; c < 4; ++c) zq[c] = ring[at(hi + 4 * c, 0)];
+    const double2 z0 = cfma(B[2], vq[2], cmul(B[0], vq[0]));
+    const double2 z1 = cfma(B[3], vq[3], cmul(B[1], vq[1]));
+    const double2 z = quad_rows_sum(cadd(z0, z1));
+    x = cfma(cneg(tau), z, x);  // the reflector's first element is 1
   }
   ub[lo] = x;  // (the four lane groups hold the same values)
   wave_lds_sync();
@@ -1270,32 +1265,25 @@ BSE_DEV double chase_bulge(double2* ring, double2* ub, int lo, int hi, int r0, b
   double2 u = cmul(scal, x);
   u.x = lo == 0 ? 1.0 : u.x;
   u.y = lo == 0 ? 0.0 : u.y;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) vq[c] = cmul(scal, xq[c]);
+  vq[0].x = hi == 0 ? 1.0 : vq[0].x;
+  vq[0].y = hi == 0 ? 0.0 : vq[0].y;
   if (!first) {
     // u^H B with the unscaled x (it does not wait for the scalars)
-    double2 g0 = czero(), g1 = czero();
-    g0 = cfmac(keep2(hi > 0, xq[0]), Bt[0], g0);
-    g1 = cfmac(xq[1], Bt[1], g1);
-    g0 = cfmac(xq[2], Bt[2], g0);
-    g1 = cfmac(xq[3], Bt[3], g1);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) zq[c] = csub(xq[c], zq[c]);  // -z, from the first column
+    xq[0] = keep2(hi > 0, xq[0]);
+    const double2 g0 = cfmac(xq[2], Bt[2], cmulc(xq[0], Bt[0]));
+    const double2 g1 = cfmac(xq[3], Bt[3], cmulc(xq[1], Bt[1]));
     const double2 ug = cfmac(scal, quad_rows_sum(cadd(g0, g1)), b0);
     const double2 ux = make_double2(fma(scal.x, xn2, al.x), fma(-scal.y, xn2, al.y));
-    const double2 uz = csub(make_double2(lane_value(ug.x, 0), lane_value(ug.y, 0)), ux);
-    const double2 G = cmulc(tn, cfmac(v, cneg(uz), ug));
-    const double ma = pick4(hi, z.x, z.y, u.x, u.y);
-    const double mr = pick4(hi, -v.x, -v.y, -G.x, G.y);
-    const double mi = pick4(hi, v.y, -v.x, -G.y, -G.x);
-    d4 re, im;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      re[c] = Bt[c].x;
-      im[c] = Bt[c].y;
-    }
-    re = __builtin_amdgcn_mfma_f64_16x16x4f64(ma, mr, re, 0, 0, 0);
-    im = __builtin_amdgcn_mfma_f64_16x16x4f64(ma, mi, im, 0, 0, 0);
+    const double2 uz = csub(ux, make_double2(lane_value(ug.x, 0), lane_value(ug.y, 0)));  // -u^H z
+    const double2 G = cmulc(cneg(tn), cfmac(v, uz, ug));
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       // the first column is known: (beta, 0, ...)
-      double2 o = make_double2(re[c], im[c]);
+      double2 o = cfma(vq[c], G, cfmac(v, zq[c], Bt[c]));
       o.x = lo ? o.x : (c == 0 && hi == 0 ? beta : 0.0);
       o.y = lo ? o.y : 0.0;
       ring[at(hi + 4 * c, lo)] = o;
@@ -1305,20 +1293,16 @@ BSE_DEV double chase_bulge(double2* ring, double2* ub, int lo, int hi, int r0, b
   ub[BW] = tn;
   tau = tn;
   v = u;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) vq[c] = cmul(scal, xq[c]);
-  vq[0].x = hi == 0 ? 1.0 : vq[0].x;
-  vq[0].y = hi == 0 ? 0.0 : vq[0].y;
   return beta;
 }
 
 // The diagonal block at rows r0 .. r0 + 15 and the probe's rows, with the reflector
 // in ub: D := H^H D H = D - u w^H - w u^H, w = tau D u - 1/2 |tau|^2 (u^H D u) u, and
-// y := H^H y.
-BSE_DEV void chase_diag(double2* ring, const double2* ub, int lo, int hi, int r0) {
+// y := H^H y.  ws: BW values of LDS.
+BSE_DEV void chase_diag(double2* ring, const double2* ub, double2* ws, int lo, int hi, int r0) {
   auto slot = [&](int c) { return ((r0 + c) & (RING - 1)) * ABS; };
   int oD[4];
-  double2 D[4], uq[4];
+  double2 D[4], uq[4], wq[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const int i = hi + 4 * c;
@@ -1328,38 +1312,32 @@ BSE_DEV void chase_diag(double2* ring, const double2* ub, int lo, int hi, int r0
   }
   const int oy = slot(lo) + 2 * BW;
   const double2 u = ub[lo], tau = ub[BW], y = ring[oy];
-  double2 q0 = czero(), q1 = czero();  // (D u)_lo = sum_i conj(D_i,lo) u_i
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const int i = hi + 4 * c;
     D[c].y = i == lo ? 0.0 : i > lo ? D[c].y : -D[c].y;
-    if (c & 1)
-      q1 = cfmac(D[c], uq[c], q1);
-    else
-      q0 = cfmac(D[c], uq[c], q0);
   }
-  const double2 sy = row_sum(cmulc(u, y));
+  // (D u)_lo = sum_i conj(D_i,lo) u_i
+  const double2 q0 = cfmac(D[2], uq[2], cmulc(D[0], uq[0]));
+  const double2 q1 = cfmac(D[3], uq[3], cmulc(D[1], uq[1]));
   const double2 q = quad_rows_sum(cadd(q0, q1));
   const double uq2 = row_sum(fma(u.x, q.x, u.y * q.y));
   const double hl = -0.5 * cabs2(tau) * uq2;
   const double2 tq = cmul(tau, q);
   const double2 w = make_double2(fma(u.x, hl, tq.x), fma(u.y, hl, tq.y));
-  const double ma = pick4(hi, u.x, u.y, w.x, w.y);
-  const double mr = pick4(hi, -w.x, -w.y, -u.x, -u.y);
-  const double mi = pick4(hi, w.y, -w.x, u.y, -u.x);
-  d4 re, im;
+  ws[lo] = w;
+  wave_lds_sync();
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    re[c] = D[c].x;
-    im[c] = D[c].y;
-  }
-  re = __builtin_amdgcn_mfma_f64_16x16x4f64(ma, mr, re, 0, 0, 0);
-  im = __builtin_amdgcn_mfma_f64_16x16x4f64(ma, mi, im, 0, 0, 0);
+  for (int c = 0; c < 4; ++c) wq[c] = ws[hi + 4 * c];
+  const double2 sy = row_sum(cmulc(u, y));
   if (hi == 0) ring[oy] = cfma(cmulc(tau, u), cneg(sy), y);
+  const double2 nu = cneg(u), nw = cneg(w);
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const int i = hi + 4 * c;
-    if (i >= lo) ring[oD[c]] = make_double2(re[c], i == lo ? 0.0 : im[c]);
+    double2 d = cfmac(nu, wq[c], cfmac(nw, uq[c], D[c]));
+    if (i == lo) d.y = 0.0;
+    if (i >= lo) ring[oD[c]] = d;
   }
 }
 
@@ -1374,7 +1352,7 @@ BSE_DEV int opaque_lane() {
 
 __global__ __launch_bounds__(CH_THREADS) void k_band_chase(BandArgs a, int np, int gmax) {
   __shared__ double2 ring[RING * ABS];
-  __shared__ double2 ub[CS][2][BW + 1];
+  __shared__ double2 ub[CS][2][BW + 1], ws[CS][BW];
   __shared__ int tick;
   constexpr int CHUNK = BW * ABS;  // values of 16 columns
   constexpr int PER = (CHUNK + 63) / 64;
@@ -1464,7 +1442,7 @@ __global__ __launch_bounds__(CH_THREADS) void k_band_chase(BandArgs a, int np, i
       for (int i = 0; i < steps; ++i) {
         const int k = i - 1 - 2 * dw, r0 = s + 1 + BW * k;
         if (s <= slast && k >= 0 && r0 < n)  // uniform
-          chase_diag(ring, ub[dw][(i & 1) ^ 1], lo, hi, r0);
+          chase_diag(ring, ub[dw][(i & 1) ^ 1], ws[dw], lo, hi, r0);
         __syncthreads();
       }
     } else if (lw < 0) {
