@@ -1147,14 +1147,16 @@ __global__ __launch_bounds__(64 * NW) void k_band_w(BandArgs a, BandFirst f, int
 
 // ------------------------------------------------------------ band storage
 // AB[c][d] = S[c + d][c] for d <= BW, zero for the diagonals that bulges will
-// use, and the probe; the
-// chase's ticket and progress words are cleared.
+// use, and the probe; the chase's ticket and progress words are cleared, also for a
+// problem that has failed: the ticket of a batch is its first problem's.
 __global__ void k_band_pack(BandArgs a, BandFirst f) {
   const int pi = band_problem(f);
   const BandProb& p = a.p[pi];
-  if (failed(p.info)) return;
   const int bx = (int)blockIdx.x - f.b[pi], nb = f.b[pi + 1] - f.b[pi];
   const int n = p.n;
+  for (int e = bx * blockDim.x + threadIdx.x; e < band_ctl_ints(n); e += nb * blockDim.x)
+    p.ctl[e] = 0;
+  if (failed(p.info)) return;
   for (int64_t e = (int64_t)bx * blockDim.x + threadIdx.x; e < (int64_t)n * ABS;
        e += (int64_t)nb * blockDim.x) {
     const int c = (int)(e / ABS), d = (int)(e % ABS);
@@ -1164,8 +1166,6 @@ __global__ void k_band_pack(BandArgs a, BandFirst f) {
     if (d == 2 * BW && p.yp) v = p.yp[c];
     p.AB[e] = v;
   }
-  for (int e = bx * blockDim.x + threadIdx.x; e < band_ctl_ints(n); e += nb * blockDim.x)
-    p.ctl[e] = 0;
 }
 
 // -------------------------------------------------------------- the chase
@@ -1362,15 +1362,22 @@ __global__ __launch_bounds__(CH_THREADS) void k_band_chase(BandArgs a, int np, i
   auto wrap = [](int e) { return e >= RING * ABS ? e - RING * ABS : e; };
   for (;;) {
     __syncthreads();
-    if (tid == 0)
-      tick = __hip_atomic_fetch_add(a.p[0].ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) {
+      // the next group of a problem that has not failed: one thread looks, since
+      // another block may set info between two wavefronts' looks
+      int t;
+      do {
+        t = __hip_atomic_fetch_add(a.p[0].ctl + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } while (t >= 0 && t < gmax * np &&
+               (t / np * CS >= max(a.p[t % np].n - 1, 1) || failed(a.p[t % np].info)));
+      tick = t;
+    }
     __syncthreads();
     const int tk = __builtin_amdgcn_readfirstlane(tick);
+    if (tk < 0 || tk >= gmax * np) return;  // every ticket is taken
     const int pi = tk % np, g = tk / np;
-    if (g >= gmax) return;  // every ticket is taken
     const BandProb& p = a.p[pi];
     const int n = p.n, s0 = g * CS;
-    if (s0 >= max(n - 1, 1) || failed(p.info)) continue;
     const __amdgpu_buffer_rsrc_t AB = __builtin_amdgcn_make_buffer_rsrc(
         (void*)p.AB, (short)0, n * ABS * (int)sizeof(double2), BUFFER_FLAGS);
     int32_t* prog = p.ctl + 2;
