@@ -34,6 +34,7 @@
 
 #include "bse_internal.h"
 #include "common.h"
+#include "mfma_tile.h"
 #include "solve_internal.h"
 #include "timing.h"
 
@@ -110,30 +111,8 @@ BSE_DEV double2* w_of(const BandProb& p, int k) {
   return p.VW + ((int64_t)(k & 1) * 2 + 1) * BW * p.n;
 }
 
-// acc + a b and acc + conj(a) b in four fused operations each
-BSE_DEV double2 cfma(double2 a, double2 b, double2 acc) {
-  return make_double2(fma(-a.y, b.y, fma(a.x, b.x, acc.x)), fma(a.y, b.x, fma(a.x, b.y, acc.y)));
-}
-BSE_DEV double2 cfmac(double2 a, double2 b, double2 acc) {
-  return make_double2(fma(a.y, b.y, fma(a.x, b.x, acc.x)), fma(-a.y, b.x, fma(a.x, b.y, acc.y)));
-}
-BSE_DEV double2 cneg(double2 a) { return make_double2(-a.x, -a.y); }
 BSE_DEV double2 czero() { return make_double2(0.0, 0.0); }
 BSE_DEV double2 keep2(bool ok, double2 v) { return make_double2(ok ? v.x : 0.0, ok ? v.y : 0.0); }
-
-// 1/x and 1/sqrt(x) for positive normal x: the hardware estimate with Newton
-// steps (short dependent chains; both end within an ulp or two).
-BSE_DEV double fast_rcp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
-}
-BSE_DEV double fast_rsq(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  const double h = 0.5 * x;
-  r = fma(r, fma(-h * r, r, 0.5), r);
-  return fma(r, fma(-h * r, r, 0.5), r);
-}
 
 template <int CTRL>
 BSE_DEV double dpp_mov(double v) {
@@ -173,24 +152,6 @@ BSE_DEV double lane_value(double v, int l) {
   const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-
-// One 16 x 16 complex accumulator on the matrix cores, Gauss's three real
-// products per complex one.  Lane l holds of an A operand's chunk c the element
-// (m = l % 16, k = l / 16 + 4 c), of a B operand's (k = l / 16 + 4 c, n = l % 16)
-// and of the result's register r (m = l / 16 + 4 r, n = l % 16): register r of a
-// result is chunk r of the same matrix as a B operand, and of its transpose as
-// an A operand.
-struct Acc {
-  d4 p1 = {0, 0, 0, 0}, p2 = {0, 0, 0, 0}, p3 = {0, 0, 0, 0};
-  BSE_DEV void mac(double2 a, double2 b) {
-    p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, p1, 0, 0, 0);
-    p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, p2, 0, 0, 0);
-    p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x + a.y, b.x + b.y, p3, 0, 0, 0);
-  }
-  BSE_DEV double2 at(int r) const {
-    return make_double2(p1[r] - p2[r], p3[r] - p1[r] - p2[r]);
-  }
-};
 
 BSE_DEV void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

@@ -23,6 +23,29 @@ BSE_DEV double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
 BSE_DEV double2 cscale(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
 BSE_DEV double cabs2(double2 a) { return a.x * a.x + a.y * a.y; }
 
+// acc + a b and acc + conj(a) b in four fused operations each
+BSE_DEV double2 cfma(double2 a, double2 b, double2 acc) {
+  return make_double2(fma(-a.y, b.y, fma(a.x, b.x, acc.x)), fma(a.y, b.x, fma(a.x, b.y, acc.y)));
+}
+BSE_DEV double2 cfmac(double2 a, double2 b, double2 acc) {
+  return make_double2(fma(a.y, b.y, fma(a.x, b.x, acc.x)), fma(-a.y, b.x, fma(a.x, b.y, acc.y)));
+}
+BSE_DEV double2 cneg(double2 a) { return make_double2(-a.x, -a.y); }
+
+// 1/x and 1/sqrt(x) for positive normal x: the hardware estimate with Newton
+// steps (short dependent chains; both end within an ulp or two).
+BSE_DEV double fast_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+BSE_DEV double fast_rsq(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  const double h = 0.5 * x;
+  r = fma(r, fma(-h * r, r, 0.5), r);
+  return fma(r, fma(-h * r, r, 0.5), r);
+}
+
 // 64-lane wavefront sum (deterministic butterfly order).
 BSE_DEV double wave_sum(double v) {
 #pragma unroll

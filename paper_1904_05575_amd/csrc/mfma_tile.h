@@ -228,3 +228,21 @@ struct ZTile {
         }
   }
 };
+
+// One 16 x 16 complex accumulator on the matrix cores, Gauss's three real
+// products per complex one.  Lane l holds of an A operand's chunk c the element
+// (m = l % 16, k = l / 16 + 4 c), of a B operand's (k = l / 16 + 4 c, n = l % 16)
+// and of the result's register r (m = l / 16 + 4 r, n = l % 16): register r of a
+// result is chunk r of the same matrix as a B operand, and of its transpose as
+// an A operand.
+struct Acc {
+  d4 p1 = {0, 0, 0, 0}, p2 = {0, 0, 0, 0}, p3 = {0, 0, 0, 0};
+  BSE_DEV void mac(double2 a, double2 b) {
+    p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, p1, 0, 0, 0);
+    p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, p2, 0, 0, 0);
+    p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x + a.y, b.x + b.y, p3, 0, 0, 0);
+  }
+  BSE_DEV double2 at(int r) const {
+    return make_double2(p1[r] - p2[r], p3[r] - p1[r] - p2[r]);
+  }
+};

@@ -14,6 +14,7 @@
 
 #include "bse_internal.h"
 #include "common.h"
+#include "mfma_tile.h"
 #include "solve_internal.h"
 #include "timing.h"
 #include "zgemm.h"
@@ -143,90 +144,113 @@ namespace {
 
 // ------------------------------------------------------------------ Cholesky
 // One panel of the blocked Cholesky A - B = U^H U (Sec. 4.3): every block
-// factors the jb x jb diagonal block A11 = U11^H U11 (right-looking; each
-// thread keeps four fixed elements in registers and only the pivot row goes
-// through LDS, one barrier per column), then solves U11^H X = A12 for its own
-// PCOLS columns of the panel row by forward substitution (one column per
-// thread, in registers; the updates of one step are independent).  Block 0
-// stores U11 into u11 (panel j0 / CH_NB holds CH_NB x CH_NB entries), not into
-// A: the other blocks may still be reading A11 when block 0 is done.
-// k_potrf_store moves every U11 into A once the factorisation is complete.
-constexpr int PCOLS = 256;
-constexpr int PEL = CH_NB * CH_NB / PCOLS;  // diagonal-block elements per thread
+// factors the jb x jb diagonal block A11 = U11^H U11 beside the identity, which
+// gives U11^-H as well, and multiplies its own PCOLS columns of the panel row A12
+// by it on the matrix cores.  The elimination is a chain of jb steps: each
+// thread keeps two elements of the block and two of the identity, and a step's
+// pivot row and column go through LDS with one barrier.  (A forward substitution
+// of the columns, one per thread, would be a second chain as long: 37-40 us a
+// panel with it.)  Block 0 stores U11 into u11 (panel j0 / CH_NB holds CH_NB x
+// CH_NB entries), not into A: the other blocks may still be reading A11 when
+// block 0 is done.  k_potrf_store moves every U11 into A once the factorisation is
+// complete.
+constexpr int PCOLS = 64;
+constexpr int PTHREADS = 512;  // four column tiles of 16, two row tiles of 16
 BSE_DEV void potrf_panel_dev(double2* __restrict__ A, int64_t ld, int64_t n, int j0, int jb,
                              double2* __restrict__ u11, int32_t* info, int bx) {
-  __shared__ double2 u[CH_NB][CH_NB + 1];  // rows of U11 as they are finished
-  __shared__ double dsh[CH_NB];
+  static_assert(CH_NB == 32 && PTHREADS == CH_NB * 16, "two elements per thread");
+  __shared__ double2 ra[2][CH_NB], ry[2][CH_NB], ca[2][CH_NB];  // two steps' buffers
+  __shared__ double2 Li[CH_NB][CH_NB + 1];                      // U11^-H
+  __shared__ double rs[CH_NB];                                  // 1 / U11[i][i]
   if (failed(info)) return;
-  const int tid = threadIdx.x;
-  const int64_t c0 = (int64_t)j0 + jb + (int64_t)bx * PCOLS;
-  const bool solve = jb == CH_NB && c0 + tid < n;
-  // this thread's column of A12 (rows j0 .. j0 + jb - 1)
-  double2 x[CH_NB];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
+  const double2 zero = make_double2(0.0, 0.0);
+  // this wavefront's tile of the panel row: columns c, rows 16 rt ..
+  const int64_t c = (int64_t)j0 + jb + (int64_t)bx * PCOLS + (wid & 3) * 16 + lo;
+  const int rt = wid >> 2;
+  const bool solve = jb == CH_NB && c < n;
+  double2 x[8];
 #pragma unroll
-  for (int r = 0; r < CH_NB; ++r)
-    x[r] = solve ? A[(int64_t)(j0 + r) + (c0 + tid) * ld] : make_double2(0.0, 0.0);
-  // elements e = tid + PCOLS q of the diagonal block: row e % 32, column e / 32
-  double2 ae[PEL];
-  int er[PEL], ec[PEL];
+  for (int k = 0; k < 8; ++k)
+    if (k < 4 || rt) x[k] = A[min((int64_t)(j0 + hi + 4 * k), n - 1) + min(c, n - 1) * ld];
+  const int i = tid >> 4;
+  double2 v[2], y[2];
 #pragma unroll
-  for (int q = 0; q < PEL; ++q) {
-    const int e = tid + PCOLS * q;
-    er[q] = e % CH_NB;
-    ec[q] = e / CH_NB;
-    const bool in = er[q] < jb && ec[q] < jb && er[q] <= ec[q];
-    ae[q] = in ? A[(int64_t)(j0 + er[q]) + (int64_t)(j0 + ec[q]) * ld] : make_double2(0.0, 0.0);
+  for (int q = 0; q < 2; ++q) {
+    const int j = (tid & 15) + 16 * q;
+    const double2 one = make_double2(i == j ? 1.0 : 0.0, 0.0);
+    v[q] = y[q] = one;
+    if (i < jb && j < jb) {
+      const double2 e = A[(int64_t)(j0 + min(i, j)) + (int64_t)(j0 + max(i, j)) * ld];
+      v[q] = i <= j ? e : cconj(e);
+    }
+    if (i == 0) {
+      ra[0][j] = v[q];
+      ry[0][j] = y[q];
+    }
+    if (j == 0) ca[0][i] = v[q];
   }
-  for (int j = 0; j < jb; ++j) {
-    // the owners of row j publish it (column >= j), then every thread updates
+  __syncthreads();
 #pragma unroll
-    for (int q = 0; q < PEL; ++q)
-      if (er[q] == j && ec[q] >= j && ec[q] < jb) u[j][ec[q]] = ae[q];
-    __syncthreads();
-    const double d = u[j][j].x;  // the same value in every thread: uniform exit
-    if (!(d > 0.0) || !isfinite(d)) {
-      if (tid == 0 && bx == 0) set_info(info, j0 + j + 1);
+  for (int s = 0; s < CH_NB; ++s) {
+    const int cur = s & 1, nxt = cur ^ 1;
+    const double d = ra[cur][s].x;  // the same value in every thread: uniform exit
+    if (s < jb && (!(d > 0.0) || !isfinite(d))) {
+      if (tid == 0 && bx == 0) set_info(info, j0 + s + 1);
       return;
     }
-    const double rd = 1.0 / d;
+    if (tid == s) rs[s] = fast_rsq(d);
+    if (s + 1 == CH_NB) break;
+    if (i > s) {
+      const double f = -fast_rcp(d);
+      const double2 l = cscale(ca[cur][i], f);
 #pragma unroll
-    for (int q = 0; q < PEL; ++q)
-      if (er[q] > j && ec[q] >= er[q] && ec[q] < jb)
-        ae[q] = csub(ae[q], cscale(cmulc(u[j][er[q]], u[j][ec[q]]), rd));
-    if (tid == 0) dsh[j] = sqrt(d);
+      for (int q = 0; q < 2; ++q) {
+        const int j = (tid & 15) + 16 * q;
+        if (j > s) v[q] = cfma(l, ra[cur][j], v[q]);
+        y[q] = cfma(l, ry[cur][j], y[q]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int j = (tid & 15) + 16 * q;
+      if (i == s + 1) {
+        ra[nxt][j] = v[q];
+        ry[nxt][j] = y[q];
+      }
+      if (j == s + 1) ca[nxt][i] = v[q];
+    }
+    __syncthreads();
   }
   __syncthreads();
-  // u holds the unscaled rows: U[j][c] = u[j][c] / sqrt(u[j][j])
-  for (int e = tid; e < CH_NB * CH_NB; e += PCOLS) {
-    const int r = e % CH_NB, c = e / CH_NB;
-    if (r < jb && c < jb && r <= c)
-      u[r][c] = (r == c) ? make_double2(dsh[r], 0.0) : cscale(u[r][c], 1.0 / dsh[r]);
-  }
-  __syncthreads();
-  if (bx == 0) {
-    double2* dst = u11 + (int64_t)(j0 / CH_NB) * CH_NB * CH_NB;
-    for (int e = tid; e < jb * jb; e += PCOLS) {
-      const int r = e % jb, c = e / jb;
-      if (r <= c) dst[r + c * CH_NB] = u[r][c];
+  // U[i][j] = v / sqrt(d_i) on and above the diagonal, U11^-H = y / sqrt(d_i) below
+  double2* dst = u11 + (int64_t)(j0 / CH_NB) * CH_NB * CH_NB;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int j = (tid & 15) + 16 * q;
+    Li[i][j] = i >= j ? cscale(y[q], rs[i]) : zero;
+    if (bx == 0 && i <= j && j < jb) {
+      const double2 u = cscale(v[q], rs[i]);
+      dst[i + j * CH_NB] = i == j ? make_double2(u.x, 0.0) : u;
     }
   }
   if (jb != CH_NB) return;  // the last panel has no panel row
-  // U11^H X = A12, right-looking: x[k] /= U[k][k]; x[r] -= conj(U[k][r]) x[k], r > k
+  // the tile's loads are complete before another wavefront stores over them
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  Acc acc;
 #pragma unroll
-  for (int k = 0; k < CH_NB; ++k) {
-    x[k] = cscale(x[k], 1.0 / u[k][k].x);
-#pragma unroll
-    for (int r = k + 1; r < CH_NB; ++r) x[r] = csub(x[r], cmulc(u[k][r], x[k]));
-  }
+  for (int k = 0; k < 8; ++k)
+    if (k < 4 || rt) acc.mac(Li[16 * rt + lo][hi + 4 * k], x[k]);
   if (solve)
 #pragma unroll
-    for (int r = 0; r < CH_NB; ++r) A[(int64_t)(j0 + r) + (c0 + tid) * ld] = x[r];
+    for (int r = 0; r < 4; ++r) A[(int64_t)(j0 + 16 * rt + hi + 4 * r) + c * ld] = acc.at(r);
 }
 
-__global__ __launch_bounds__(PCOLS) void k_potrf_panel(double2* __restrict__ A, int64_t ld,
-                                                       int64_t n, int j0, int jb,
-                                                       double2* __restrict__ u11,
-                                                       int32_t* info) {
+__global__ __launch_bounds__(PTHREADS) void k_potrf_panel(double2* __restrict__ A, int64_t ld,
+                                                          int64_t n, int j0, int jb,
+                                                          double2* __restrict__ u11,
+                                                          int32_t* info) {
   potrf_panel_dev(A, ld, n, j0, jb, u11, info, (int)blockIdx.x);
 }
 
@@ -236,7 +260,7 @@ __global__ __launch_bounds__(PCOLS) void k_potrf_panel(double2* __restrict__ A, 
 struct PotrfGroup {
   CholItem it[CHOL_GROUP_MAX];
 };
-__global__ __launch_bounds__(PCOLS) void k_potrf_panel_b(PotrfGroup g, int j0) {
+__global__ __launch_bounds__(PTHREADS) void k_potrf_panel_b(PotrfGroup g, int j0) {
   const CholItem& q = g.it[blockIdx.y];
   if (j0 >= q.n) return;
   const int jb = (int)min<int64_t>(CH_NB, q.n - j0);
@@ -1282,7 +1306,7 @@ bool cholesky(double2* H1, int64_t n, int64_t ld, double2* u11, int32_t* info, h
     const int jb = (int)std::min<int64_t>(CH_NB, n - j0);
     const int64_t j1 = j0 + jb, rest1 = n - j1;
     BSE_LAUNCH(k_potrf_panel, dim3((unsigned)std::max<int64_t>(1, cdiv(rest1, PCOLS))),
-               dim3(PCOLS), 0, s, H1, ld, n, (int)j0, jb, u11, info);
+               dim3(PTHREADS), 0, s, H1, ld, n, (int)j0, jb, u11, info);
     if (rest1 <= 0) break;
     const int jb2 = (int)std::min<int64_t>(CH_NB, rest1);
     const int64_t j2 = j1 + jb2, rest2 = n - j2;
@@ -1290,7 +1314,7 @@ bool cholesky(double2* H1, int64_t n, int64_t ld, double2* u11, int32_t* info, h
     if (!herk_update(H1, ld, j0, jb, j1, jb2, j1, (int)rest1, tile, "zgemm_potrf_rows", info, s))
       return false;
     BSE_LAUNCH(k_potrf_panel, dim3((unsigned)std::max<int64_t>(1, cdiv(rest2, PCOLS))),
-               dim3(PCOLS), 0, s, H1, ld, n, (int)j1, jb2, u11, info);
+               dim3(PTHREADS), 0, s, H1, ld, n, (int)j1, jb2, u11, info);
     if (rest2 <= 0) break;
     // trailing matrix: rows and columns j2 .. n-1, K = jb + jb2
     if (!herk_update(H1, ld, j0, jb + jb2, j2, (int)rest2, j2, (int)rest2, tile,
@@ -1352,7 +1376,7 @@ bool cholesky_batch(const CholItem* it, int np, hipStream_t s) {
       gx = std::max(gx, rest > 0 ? cdiv(rest, PCOLS) : 1);
     }
     if (gx > 0)
-      BSE_LAUNCH(k_potrf_panel_b, dim3((unsigned)gx, (unsigned)np), dim3(PCOLS), 0, s, g,
+      BSE_LAUNCH(k_potrf_panel_b, dim3((unsigned)gx, (unsigned)np), dim3(PTHREADS), 0, s, g,
                  (int)j0);
   };
   for (int64_t j0 = 0; j0 < nmax; j0 += 2 * CH_NB) {
