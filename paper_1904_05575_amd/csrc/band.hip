@@ -114,22 +114,6 @@ BSE_DEV double2* w_of(const BandProb& p, int k) {
 BSE_DEV double2 czero() { return make_double2(0.0, 0.0); }
 BSE_DEV double2 keep2(bool ok, double2 v) { return make_double2(ok ? v.x : 0.0, ok ? v.y : 0.0); }
 
-template <int CTRL>
-BSE_DEV double dpp_mov(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-// Sum over the 16 lanes of each row; every lane of the row gets it.
-BSE_DEV double row_sum(double v) {
-  v += dpp_mov<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp_mov<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp_mov<0x141>(v);  // row_half_mirror
-  v += dpp_mov<0x140>(v);  // row_mirror
-  return v;
-}
-BSE_DEV double2 row_sum(double2 v) { return make_double2(row_sum(v.x), row_sum(v.y)); }
 // Sum over the four rows (lanes l, l ^ 16, l ^ 32, l ^ 48); every lane gets it.
 BSE_DEV double quad_rows_sum(double v) {
   const long long b = __double_as_longlong(v);
@@ -151,11 +135,6 @@ BSE_DEV double lane_value(double v, int l) {
   const int lo = __builtin_amdgcn_readlane((int)b, l);
   const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-BSE_DEV void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 // Sum of `nb` blocks' 16 x 16 partials into out (256 values, LDS); tmp: 256

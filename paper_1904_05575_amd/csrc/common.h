@@ -46,6 +46,29 @@ BSE_DEV double fast_rsq(double x) {
   return fma(r, fma(-h * r, r, 0.5), r);
 }
 
+// What a wavefront wrote to LDS before is there for its own reads after.
+BSE_DEV void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+template <int CTRL>
+BSE_DEV double dpp_mov(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// Sum over the 16 lanes of each row; every lane of the row gets it.
+BSE_DEV double row_sum(double v) {
+  v += dpp_mov<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp_mov<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_mov<0x141>(v);  // row_half_mirror
+  v += dpp_mov<0x140>(v);  // row_mirror
+  return v;
+}
+BSE_DEV double2 row_sum(double2 v) { return make_double2(row_sum(v.x), row_sum(v.y)); }
+
 // 64-lane wavefront sum (deterministic butterfly order).
 BSE_DEV double wave_sum(double v) {
 #pragma unroll
