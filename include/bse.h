@@ -399,7 +399,7 @@ int64_t bse_timing_report(char* buf, int64_t len);
  *                          choice = real matrix-core products per complex one
  *                          on 16- and 32-edge tiles: 4 (re = ar br - ai bi,
  *                          im = ar bi + ai br) or 3 (Gauss: ar br, ai bi,
- *                          (ar + ai)(br + bi)); 64-edge tiles always take 4
+ *                          (ar + ai)(br + bi)); 64-edge tiles always take 3
  *   BSE_TUNE_BATCH_SWEEP, BSE_TUNE_BATCH_ALIGN  of an earlier batched
  *                          reduction: choices 0, 1, 2 or 4 and 0 or 1 are
  *                          accepted and have no effect

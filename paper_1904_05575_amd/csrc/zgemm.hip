@@ -203,9 +203,14 @@ int tile_edge(const ZgemmParams& p, int batch) {
 
 }  // namespace
 
-// Gauss's three products take a third more accumulators; measured at N = 6144
-// they pay on the 16- and 32-edge tiles (Householder and Cholesky updates,
-// exchange) and lose on the 64-edge tile, whose four-product form is kept.
+// The products are bound by the matrix cores (about 50 TFLOP/s of FP64 products is
+// what they sustain), so Gauss's three products in place of four are a quarter less
+// time where the third accumulator leaves enough wavefronts: 64-edge tiles take eight
+// wavefronts of 16 x 32 (48 accumulator registers).  At N = 6144, four products on four
+// wavefronts of 32 x 32 / three on the same / three on eight: U (A+B) 18.3 / 22.3 / 14.1
+// ms, its product with U^H 6.1 / 7.3 / 4.6 ms, the Cholesky updates 9.9 / 12.8 / 7.3 ms
+// (N = 2000: 0.76 / 0.85 / 0.55, 0.49 / 0.39 / 0.32, 0.59 / 0.65 / 0.52 ms); tiles of
+// 128 x 64 and 128 x 128 gain nothing on that.
 // Each item takes the tile edge and the products per complex one that zgemm()
 // would take for it alone, so that its values are those of that call; items
 // sharing both go into one launch.
@@ -221,7 +226,7 @@ hipError_t zgemm_group(const ZgemmParams& base, const ZgemmItem* items, int coun
                                     : tune_choice(BSE_TUNE_GEMM_PRODUCTS,
                                                   std::max(one.M, one.N), 3);
     const int edge = tile_edge(one, 1);
-    key[i] = edge * 8 + (edge == 64 ? 4 : prods);
+    key[i] = edge * 8 + (edge == 64 ? 3 : prods);
   }
   std::vector<char> done(count, 0);
   for (int i = 0; i < count; ++i) {
@@ -248,7 +253,7 @@ hipError_t zgemm_group(const ZgemmParams& base, const ZgemmItem* items, int coun
         e = launch_group<32, 32, 2, 2, false>(base, g, ng, s);
         break;
       default:
-        e = launch_group<64, 64, 2, 2, false>(base, g, ng, s);
+        e = launch_group<64, 64, 4, 2, true>(base, g, ng, s);
     }
     if (e != hipSuccess) return e;  // items of this key past the first launch: later in the loop
   }
@@ -267,6 +272,6 @@ hipError_t zgemm(const ZgemmParams& p, int batch, hipStream_t s) {
       return prods == 3 ? launch<32, 32, 2, 2, true>(p, batch, s)
                         : launch<32, 32, 2, 2, false>(p, batch, s);
     default:
-      return launch<64, 64, 2, 2, false>(p, batch, s);
+      return launch<64, 64, 4, 2, true>(p, batch, s);
   }
 }
