@@ -9,6 +9,7 @@
 // v^1/2 (v^1/2 eps v^-1/2)^-1 v^1/2.
 #include "bse_internal.h"
 #include "common.h"
+#include "mfma_tile.h"
 #include "timing.h"
 #include "zgemm.h"
 
@@ -56,35 +57,40 @@ __global__ __launch_bounds__(256) void k_screen_weights(int nk, int nv, int nc,
 // slice) and every wavefront accumulates its share of the NT(NT+1)/2 upper
 // 16 x 16 output tiles on MFMA (the A and B operands are the same rows, A
 // conjugated and weighted).  Each pair element is read from HBM once.
+// Bound by the matrix cores of one compute unit per q: Gauss's three products per
+// complex one, and eight wavefronts (tiles dealt so that every SIMD has as many) for the
+// reads from LDS to overlap with products.  216 q of 2 x 1728 rows, N_G = 113: 0.98 ms
+// (1.22 ms with four products and one wavefront per SIMD).
 template <int NT>
-__global__ __launch_bounds__(256) void k_screen_chi(const double2* __restrict__ S1,
+__global__ __launch_bounds__(512) void k_screen_chi(const double2* __restrict__ S1,
                                                     const double2* __restrict__ S2,
                                                     const double* __restrict__ w1,
                                                     const double* __restrict__ w2, int64_t k1,
                                                     int ng, double2* __restrict__ W,
                                                     const int32_t* info) {
   constexpr int NP = NT * 16, PITCH = NP + 2, RS = 16;  // rows per slice
-  constexpr int T = NT * (NT + 1) / 2, TW = (T + 3) / 4, EL = NT;  // EL = RS * NP / 256
+  constexpr int T = NT * (NT + 1) / 2, TW = (T + 7) / 8, EL = (RS * NP + 511) / 512;
   __shared__ double sre[2][RS][PITCH], sim[2][RS][PITCH];
   __shared__ double sw[2][RS];
   if (failed(info)) return;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t q = blockIdx.x;
   // the columns beyond N_G stay zero in both buffers
-  for (int e = tid; e < 2 * RS * NP; e += 256) {
+  for (int e = tid; e < 2 * RS * NP; e += 512) {
     const int b = e / (RS * NP), r = (e / NP) % RS, c = e % NP;
     if (c >= ng) {
       sre[b][r][c] = 0.0;
       sim[b][r][c] = 0.0;
     }
   }
-  // this wavefront's tiles: t = wid, wid + 4, ... in row-major order over I <= J
+  // this wavefront's tiles: t = wid, wid + 8, ... in row-major order over I <= J
   int tI[TW], tJ[TW];
   bool tok[TW];
-  d4 cr[TW], ci[TW];
+  Acc acc[TW];
 #pragma unroll
   for (int u = 0; u < TW; ++u) {
-    const int t = wid + 4 * u;
+    const int t = wid + 8 * u;
     tok[u] = t < T;
     int I = 0, rem = tok[u] ? t : 0;
     while (rem >= NT - I) {
@@ -93,8 +99,6 @@ __global__ __launch_bounds__(256) void k_screen_chi(const double2* __restrict__ 
     }
     tI[u] = I;
     tJ[u] = I + rem;
-    cr[u] = d4{0, 0, 0, 0};
-    ci[u] = d4{0, 0, 0, 0};
   }
   const int slice_el = RS * ng;
   double2 pre[EL];
@@ -107,7 +111,7 @@ __global__ __launch_bounds__(256) void k_screen_chi(const double2* __restrict__ 
       const int64_t row0 = sl * RS;
 #pragma unroll
       for (int e = 0; e < EL; ++e) {
-        const int idx = tid + 256 * e;
+        const int idx = tid + 512 * e;
         const int r = idx / ng;
         const bool ok = idx < slice_el && row0 + r < k1;
         pre[e] = ok ? M[row0 * ng + idx] : make_double2(0.0, 0.0);
@@ -117,7 +121,7 @@ __global__ __launch_bounds__(256) void k_screen_chi(const double2* __restrict__ 
     auto put = [&](int b) {
 #pragma unroll
       for (int e = 0; e < EL; ++e) {
-        const int idx = tid + 256 * e;
+        const int idx = tid + 512 * e;
         if (idx < slice_el) {
           const int r = idx / ng, c = idx % ng;
           sre[b][r][c] = pre[e].x;
@@ -140,12 +144,8 @@ __global__ __launch_bounds__(256) void k_screen_chi(const double2* __restrict__ 
         for (int u = 0; u < TW; ++u) {
           if (!tok[u]) continue;  // uniform in the wavefront
           const int ca = tI[u] * 16 + (lane & 15), cb = tJ[u] * 16 + (lane & 15);
-          const double are = wk * sre[buf][k][ca], aim = -wk * sim[buf][k][ca];
-          const double bre = sre[buf][k][cb], bim = sim[buf][k][cb];
-          cr[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(are, bre, cr[u], 0, 0, 0);
-          cr[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-aim, bim, cr[u], 0, 0, 0);
-          ci[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(are, bim, ci[u], 0, 0, 0);
-          ci[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(aim, bre, ci[u], 0, 0, 0);
+          acc[u].mac(make_double2(wk * sre[buf][k][ca], -wk * sim[buf][k][ca]),
+                     make_double2(sre[buf][k][cb], sim[buf][k][cb]));
         }
       }
       buf ^= 1;
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void k_screen_chi(const double2* __restrict__ 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int gi = tI[u] * 16 + (lane >> 4) + 4 * r, gj = tJ[u] * 16 + (lane & 15);
-      if (gi < ng && gj < ng) Wq[(int64_t)gi * ng + gj] = make_double2(cr[u][r], ci[u][r]);
+      if (gi < ng && gj < ng) Wq[(int64_t)gi * ng + gj] = acc[u].at(r);
     }
   }
 }
@@ -233,14 +233,21 @@ __global__ __launch_bounds__(256) void k_screen_invert(double2* __restrict__ W,
 // (ti, tj) of a 16 x 32 grid holds the elements (ti + 16 a, tj + 32 b),
 // a < 8, b < 4, so a thread needs 8 entries of the pivot column and 4 of the
 // pivot row per step.  Per pivot k the owners publish row k and column k in
-// LDS and every thread updates its own elements: two barriers per pivot and
-// no global traffic between the load and the final store.  The lower
-// triangle is formed from the conjugate of the upper one when it is loaded.
+// LDS and every thread updates its own elements: one barrier per pivot (two
+// buffers in turn) and no global traffic between the load and the final store.
+// The lower triangle is formed from the conjugate of the upper one when it is
+// loaded; elements past N_G are zero and stay zero.
+// Bound by the vector ALU: 4 FMA per element and pivot.  The pivots go in groups of
+// 16, so that the registers of row and column k are known when the code is written,
+// and row and column take the same update as the rest,
+//   a_ij = a_ij - c_i r_j,  a_ij = 0 and c_k = -1/d in row k, 0 and r_k = -1 in column k
+// (c_i = a_ik / d, r_j = a_kj).  216 matrices, N_G = 113: 0.15 ms (0.52 ms with the
+// row and the column told apart for each element).
 constexpr int INV_NGMAX = 128, INV_TI = 16, INV_TJ = 32;
 constexpr int INV_A = INV_NGMAX / INV_TI, INV_B = INV_NGMAX / INV_TJ;
 __global__ __launch_bounds__(INV_TI * INV_TJ) void k_screen_invert_reg(
     double2* __restrict__ W, const double* __restrict__ vsqrt, int ng, int32_t* info) {
-  __shared__ double2 col[INV_NGMAX], row[INV_NGMAX];
+  __shared__ double2 col[2][INV_NGMAX], row[2][INV_NGMAX];
   __shared__ double s[INV_NGMAX];
   if (failed(info)) return;
   const int tid = threadIdx.x, ti = tid % INV_TI, tj = tid / INV_TI;
@@ -261,42 +268,61 @@ __global__ __launch_bounds__(INV_TI * INV_TJ) void k_screen_invert_reg(
                                i == j ? 0.0 : s[i] * v.y * s[j]);
       }
     }
-  for (int k = 0; k < ng; ++k) {
+  bool bad = false;
+  auto pivots = [&](auto block) __attribute__((always_inline)) {
+    constexpr int X = block.value, Y = X * INV_TI / INV_TJ;  // registers of row and column k
+    for (int k = X * INV_TI; k < min(ng, (X + 1) * INV_TI); ++k) {
+      const bool mr = ti == k % INV_TI, mc = tj == k % INV_TJ;  // this thread has row, column k
+      double2* cb = col[k & 1];
+      double2* rb = row[k & 1];
+      if (mc) {
 #pragma unroll
-    for (int x = 0; x < INV_A; ++x)
-#pragma unroll
-      for (int y = 0; y < INV_B; ++y) {
-        const int i = ti + INV_TI * x, j = tj + INV_TJ * y;
-        if (j == k && i < ng) col[i] = a[x][y];
-        if (i == k && j < ng) row[j] = a[x][y];
+        for (int x = 0; x < INV_A; ++x) cb[ti + INV_TI * x] = a[x][Y];
       }
-    __syncthreads();
-    const double2 d = row[k];
-    if (!(d.x > 0.0) || !isfinite(d.x)) {
-      if (tid == 0) set_info(info, -6);
-      return;  // uniform: every thread reads the same pivot
+      if (mr) {
+#pragma unroll
+        for (int y = 0; y < INV_B; ++y) rb[tj + INV_TJ * y] = a[X][y];
+      }
+      __syncthreads();
+      const double2 d = rb[k];
+      if (!(d.x > 0.0) || !isfinite(d.x)) {  // uniform: every thread reads the same pivot
+        bad = true;
+        return;
+      }
+      const double dn = 1.0 / cabs2(d);
+      const double2 rd = make_double2(d.x * dn, -d.y * dn);  // 1 / d
+      double2 c[INV_A], r[INV_B];
+#pragma unroll
+      for (int x = 0; x < INV_A; ++x) c[x] = cmul(cb[ti + INV_TI * x], rd);
+#pragma unroll
+      for (int y = 0; y < INV_B; ++y) r[y] = rb[tj + INV_TJ * y];
+      if (mr) {
+        c[X] = cneg(rd);
+#pragma unroll
+        for (int y = 0; y < INV_B; ++y) a[X][y] = make_double2(0.0, 0.0);
+      }
+      if (mc) {
+        r[Y] = make_double2(-1.0, 0.0);
+#pragma unroll
+        for (int x = 0; x < INV_A; ++x) a[x][Y] = make_double2(0.0, 0.0);
+      }
+#pragma unroll
+      for (int x = 0; x < INV_A; ++x)
+#pragma unroll
+        for (int y = 0; y < INV_B; ++y) a[x][y] = cfma(cneg(c[x]), r[y], a[x][y]);
     }
-    const double dn = 1.0 / cabs2(d);
-    const double2 rd = make_double2(d.x * dn, -d.y * dn);  // 1 / d
-    double2 cd[INV_A], rw[INV_B];
-#pragma unroll
-    for (int x = 0; x < INV_A; ++x) cd[x] = cmul(col[min(ti + INV_TI * x, INV_NGMAX - 1)], rd);
-#pragma unroll
-    for (int y = 0; y < INV_B; ++y) rw[y] = row[min(tj + INV_TJ * y, INV_NGMAX - 1)];
-#pragma unroll
-    for (int x = 0; x < INV_A; ++x)
-#pragma unroll
-      for (int y = 0; y < INV_B; ++y) {
-        const int i = ti + INV_TI * x, j = tj + INV_TJ * y;
-        if (i >= ng || j >= ng) continue;
-        if (i == k && j == k)
-          a[x][y] = make_double2(-rd.x, -rd.y);
-        else if (i == k || j == k)
-          a[x][y] = cmul(a[x][y], rd);
-        else
-          a[x][y] = csub(a[x][y], cmul(cd[x], rw[y]));
-      }
-    __syncthreads();  // col and row are rewritten for the next pivot
+  };
+  pivots(std::integral_constant<int, 0>{});
+  if (!bad) pivots(std::integral_constant<int, 1>{});
+  if (!bad) pivots(std::integral_constant<int, 2>{});
+  if (!bad) pivots(std::integral_constant<int, 3>{});
+  if (!bad) pivots(std::integral_constant<int, 4>{});
+  if (!bad) pivots(std::integral_constant<int, 5>{});
+  if (!bad) pivots(std::integral_constant<int, 6>{});
+  if (!bad) pivots(std::integral_constant<int, 7>{});
+  if (bad) {
+    if (tid == 0) set_info(info, -6);
+    return;
   }
 #pragma unroll
   for (int x = 0; x < INV_A; ++x)
@@ -324,7 +350,7 @@ bse_status screening_run(const bse_screen_desc* d, const double* eps_v, const do
   double* w2 = w1 + (int64_t)nk * k1;
   BSE_LAUNCH(k_screen_weights, dim3((unsigned)cdiv(2 * nk * k1, 256)), dim3(256), 0, s, nk,
              d->nv, d->nc, eps_v, eps_c, kqmap, d->inv_vc * d->units_per_hartree, w1, w2, info);
-  const dim3 g1((unsigned)nk), b1(256);
+  const dim3 g1((unsigned)nk), b1(512);
   switch (cdiv(ng, 16)) {  // one block per q streams its rows once (N_G <= 128)
     case 1: BSE_LAUNCH(k_screen_chi<1>, g1, b1, 0, s, Svc, Scv, w1, w2, k1, ng, W, info); break;
     case 2: BSE_LAUNCH(k_screen_chi<2>, g1, b1, 0, s, Svc, Scv, w1, w2, k1, ng, W, info); break;
