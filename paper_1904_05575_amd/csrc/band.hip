@@ -63,6 +63,14 @@ __host__ __device__ inline int panel_blocks(int64_t m) { return cdiv(m, panel_ro
 // 2048, both kernels, small tiles up to 512, 768, 1024, 1408: 4.76, 4.76, 4.80, 4.94 ms).
 constexpr int STEP_SMALL = 512;
 __host__ __device__ inline int step_tile(int64_t m) { return m > STEP_SMALL ? 64 : 32; }
+// Halves of a tile's rows: beyond STEP_TALL a block takes tiles of 128 rows x 64
+// columns, whose halves add their column sums in LDS, so that half the slots are written
+// and read (16 KB per tile of 64 KB, each way).  k_band_step itself does not gain (its two
+// more barriers per tile), k_band_x does where the slots leave the caches.  Both kernels,
+// tall tiles never, beyond 3072, 2048, 1024: n = 2048: 4.72, 4.82, 4.75, 4.98 ms; n = 4200:
+// 17.5, 17.2, 17.1, 17.4 ms; n = 6144: 42.0, 40.0, 39.8, 40.2 ms (n = 10368: 176 -> 151).
+constexpr int STEP_TALL = 2048;
+__host__ __device__ inline int step_halves(int64_t m) { return m > STEP_TALL ? 2 : 1; }
 
 __host__ __device__ inline int band_ctl_ints(int n) { return 2 + n / CHASE_SWEEPS + 1; }
 
@@ -689,37 +697,48 @@ __global__ __launch_bounds__(64 * NW) void k_band_panel(BandArgs a, BandFirst f,
 }
 
 // ------------------------------------------------ trailing update and S V
-// Tiles of the lower triangle of the trailing matrix (order m from row t), ST x
-// ST in tile-row order; block b of G takes the run [T b / G, T (b+1) / G).  A
-// tile-row's part inside one run is a piece.  Row r of tile-row Ir collects
+// Tiles of the lower triangle of the trailing matrix (order m from row t), RH ST x
+// ST in tile-row order, RH (I + 1) of them in tile-row I; block b of G takes the run
+// [T b / G, T (b+1) / G).  A tile-row's part inside one run is a piece.  Row r of
+// tile-row Ir collects
 //   Y[p][r]        p = 0 .. nrs - 1   the pieces of tile-row Ir: S V over them
-//   Y[ycs + I][r]  I = Ir .. nI - 1   tile (I, Ir): S_{I,Ir}^H V_I
+//   Y[ycs + I][r]  I = Ir .. nI - 1   tile (I, r / ST): S^H V_I
 __host__ __device__ inline int64_t run_start(int64_t T, int G, int b) { return T * b / G; }
 __host__ __device__ inline int block_of(int64_t T, int G, int64_t t) {
   return (int)(((t + 1) * G - 1) / T);
 }
 
-template <int ST>
-struct StepSmem {
-  double2 v[ST][LDT], w[ST][LDT];  // previous panel's V and W, the tile-row's rows
-  double2 x[ST][LDT];              // this panel's V
-  double2 tr[ST / 16][16 * LDT];   // per wavefront: a 16 x 16 block, transposed
+// CODE = ST RH: tiles of ST columns and RH ST rows.
+template <int CODE>
+struct StepShape {
+  static constexpr int ST = CODE > 64 ? 64 : CODE, RH = CODE / ST, RT = RH * ST;
 };
 
-// Wavefront w of a block: tile columns 16 w .. 16 w + 15.
-template <int ST>
-__global__ __launch_bounds__(4 * ST, 2) void k_band_step(BandArgs a, BandFirst f, int k) {
-  constexpr int SR = ST / 16;              // 16-row blocks of a tile, wavefronts of a block
-  constexpr int STEP_THREADS = 64 * SR;
+template <int ST, int RH>
+struct StepSmem {
+  double2 v[RH * ST][LDT], w[RH * ST][LDT];  // previous panel's V and W, the tile-row's rows
+  double2 x[RH * ST][LDT];                   // this panel's V
+  double2 tr[RH * ST / 16][16 * LDT];        // per wavefront: a 16 x 16 block, transposed
+  double2 col[RH > 1 ? ST / 16 : 1][256];    // the lower half's column sums
+};
+
+// Wavefront w of a block: tile columns 16 wc .. 16 wc + 15 of the row half rh, w = rh SR + wc.
+template <int CODE>
+__global__ __launch_bounds__(4 * CODE, 2) void k_band_step(BandArgs a, BandFirst f, int k) {
+  constexpr int ST = StepShape<CODE>::ST, RH = StepShape<CODE>::RH, RT = StepShape<CODE>::RT;
+  constexpr int SR = ST / 16;              // 16-row blocks of a half, its wavefronts
+  constexpr int STEP_THREADS = 64 * SR * RH;
   const int pi = band_problem(f);
   const BandProb& p = a.p[pi];
   if (failed(p.info)) return;
   const int bx = (int)blockIdx.x - f.b[pi], G = f.b[pi + 1] - f.b[pi];
-  const int t = BW * (k + 1), n = p.n, nI = cdiv(n - t, ST);
-  const int64_t T = (int64_t)nI * (nI + 1) / 2, N16 = (int64_t)n * BW, ld = p.ld;
+  const int t = BW * (k + 1), n = p.n, nI = cdiv(n - t, RT);
+  const int64_t T = (int64_t)RH * nI * (nI + 1) / 2, N16 = (int64_t)n * BW, ld = p.ld;
   const int64_t t_end = run_start(T, G, bx + 1);
-  __shared__ StepSmem<ST> sm;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
+  __shared__ StepSmem<ST, RH> sm;
+  const int tid = threadIdx.x, lane = tid & 63, lo = lane & 15, hi = lane >> 4;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wc = wid % SR, rh = wid / SR;
   const bool upd = k > 0;  // a previous panel to apply
   const double2* __restrict__ Vn = v_of(p, k);
   const double2* __restrict__ Vp = v_of(p, k - 1);
@@ -728,14 +747,14 @@ __global__ __launch_bounds__(4 * ST, 2) void k_band_step(BandArgs a, BandFirst f
   double2* __restrict__ Y = p.Y;
 
   int64_t tt = run_start(T, G, bx);
-  int I = (int)((sqrt(8.0 * (double)tt + 1.0) - 1.0) * 0.5);
-  if ((int64_t)(I + 1) * (I + 2) / 2 <= tt) ++I;
-  if ((int64_t)I * (I + 1) / 2 > tt) --I;
-  int J = (int)(tt - (int64_t)I * (I + 1) / 2);
+  int I = (int)((sqrt(8.0 * (double)(tt / RH) + 1.0) - 1.0) * 0.5);
+  if ((int64_t)(I + 1) * (I + 2) / 2 <= tt / RH) ++I;
+  if ((int64_t)I * (I + 1) / 2 > tt / RH) --I;
+  int J = (int)(tt - (int64_t)RH * I * (I + 1) / 2);
 
   auto stage_rows = [&]() {  // the tile-row's rows of V, W and this panel's V
-    for (int e = tid; e < ST * BW; e += STEP_THREADS) {
-      const int r = e >> 4, c = e & 15, row = t + I * ST + r;
+    for (int e = tid; e < RT * BW; e += STEP_THREADS) {
+      const int r = e >> 4, c = e & 15, row = t + I * RT + r;
       const int64_t at = (int64_t)min(row, n - 1) * BW + c;
       const bool ok = row < n;
       sm.x[r][c] = keep2(ok, Vn[at]);
@@ -745,11 +764,11 @@ __global__ __launch_bounds__(4 * ST, 2) void k_band_step(BandArgs a, BandFirst f
       }
     }
   };
-  // block (rs, wid) of tile (I, J), as the transposed 16 x 16 block: register r
+  // block (rs, wc) of the half of tile (I, J), as the transposed 16 x 16 block: register r
   // of lane l holds row l % 16, column l / 16 + 4 r
   auto load = [&](double2(&s)[4], int I_, int J_, int rs) {
-    const int64_t row = min(t + I_ * ST + rs * 16 + lo, n - 1);
-    const int c0 = t + J_ * ST + wid * 16 + hi;
+    const int64_t row = min(t + I_ * RT + rh * ST + rs * 16 + lo, n - 1);
+    const int c0 = t + J_ * ST + wc * 16 + hi;
 #pragma unroll
     for (int r = 0; r < 4; ++r) s[r] = M[row + (int64_t)min(c0 + 4 * r, n - 1) * ld];
   };
@@ -760,7 +779,7 @@ __global__ __launch_bounds__(4 * ST, 2) void k_band_step(BandArgs a, BandFirst f
   load(s, I, J, 0);
   __syncthreads();
   while (tt < t_end) {  // uniform
-    const int cj = t + J * ST + wid * 16;  // first column of this wavefront
+    const int cj = t + J * ST + wc * 16;  // first column of this wavefront
     // this wavefront's columns of the operands
     double2 aw[4], av[4], ax[4];
 #pragma unroll
@@ -773,7 +792,8 @@ __global__ __launch_bounds__(4 * ST, 2) void k_band_step(BandArgs a, BandFirst f
       }
       ax[c] = keep2(okk, Vn[(int64_t)min(cj + hi + 4 * c, n - 1) * BW + lo]);
     }
-    const int In = J + 1 > I ? I + 1 : I, Jn = J + 1 > I ? 0 : J + 1;
+    const bool row_end = J + 1 == RH * (I + 1);
+    const int In = row_end ? I + 1 : I, Jn = row_end ? 0 : J + 1;
     const bool more = tt + 1 < t_end;
     Acc col;
 #pragma unroll
@@ -783,16 +803,17 @@ __global__ __launch_bounds__(4 * ST, 2) void k_band_step(BandArgs a, BandFirst f
         load(sn, I, J, rs + 1);
       else
         load(sn, more ? In : I, more ? Jn : J, 0);
-      const bool below = I != J || rs > wid, diag = I == J && rs == wid;  // uniform
+      const int off = ((I * RH + rh) - J) * SR + rs - wc;  // 16-row blocks below the diagonal
+      const bool below = off > 0, diag = off == 0;         // uniform
       if (below || diag) {
-        const int r0 = rs * 16;
+        const int r0 = rh * ST + rs * 16;
         if (upd) {
           Acc u;
 #pragma unroll
           for (int c = 0; c < 4; ++c) u.mac(aw[c], sm.v[r0 + lo][hi + 4 * c]);
 #pragma unroll
           for (int c = 0; c < 4; ++c) u.mac(av[c], sm.w[r0 + lo][hi + 4 * c]);
-          const int row = t + I * ST + r0 + lo;
+          const int row = t + I * RT + r0 + lo;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             s[r] = csub(s[r], u.at(r));
@@ -826,18 +847,30 @@ __global__ __launch_bounds__(4 * ST, 2) void k_band_step(BandArgs a, BandFirst f
 #pragma unroll
       for (int r = 0; r < 4; ++r) s[r] = sn[r];
     }
-    // S_IJ^H V_I: [vec][column] of this wavefront's 16 columns
-    if (cj + lo < n) {
+    // S_IJ^H V_I: [vec][column] of this wavefront's 16 columns, the lower half's through LDS
+    if constexpr (RH > 1) {
+      __syncthreads();  // the previous tile's are read
+      if (rh > 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sm.col[wc][(hi + 4 * r) * 16 + lo] = col.at(r);
+      }
+      __syncthreads();
+    }
+    if (rh == 0 && cj + lo < n) {
       double2* y = Y + (int64_t)(p.ycs + I) * N16 + (int64_t)(cj + lo) * BW;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) y[hi + 4 * r] = col.at(r);
+      for (int r = 0; r < 4; ++r) {
+        double2 v = col.at(r);
+        if constexpr (RH > 1) v = cadd(v, sm.col[wc][(hi + 4 * r) * 16 + lo]);
+        y[hi + 4 * r] = v;
+      }
     }
-    if (J == I || !more) {
+    if (row_end || !more) {
       // end of a piece: the wavefronts' row sums, two 16-row blocks at a time
       // through the operand rows' space
-      double2* red = &sm.v[0][0];  // SR x 2 x 256 values of the 3 ST LDT there are
-      static_assert(SR * 2 * 256 <= 3 * ST * LDT, "row sums fit in the operand rows");
-      const int slot = bx - block_of(T, G, (int64_t)I * (I + 1) / 2);
+      double2* red = &sm.v[0][0];  // RH x SR x 2 x 256 values of the 3 RT LDT there are
+      static_assert(RH * SR * 2 * 256 <= 3 * RT * LDT, "row sums fit in the operand rows");
+      const int slot = bx - block_of(T, G, (int64_t)RH * I * (I + 1) / 2);
       double2* y = Y + (int64_t)slot * N16;
 #pragma unroll
       for (int half = 0; half < SR / 2; ++half) {
@@ -848,11 +881,12 @@ __global__ __launch_bounds__(4 * ST, 2) void k_band_step(BandArgs a, BandFirst f
           for (int r = 0; r < 4; ++r)
             red[(wid * 2 + q) * 256 + lo * BW + hi + 4 * r] = row_acc[2 * half + q].at(r);
         __syncthreads();
-        for (int e = tid; e < 2 * 256; e += STEP_THREADS) {
-          const int row = t + I * ST + half * 32 + (e >> 4);
+        for (int e = tid; e < RH * 512; e += STEP_THREADS) {
+          const int q = e >> 9;  // row half
+          const int row = t + I * RT + q * ST + half * 32 + ((e & 511) >> 4);
           double2 o = czero();
 #pragma unroll
-          for (int w = 0; w < SR; ++w) o = cadd(o, red[w * 512 + e]);
+          for (int w = 0; w < SR; ++w) o = cadd(o, red[(q * SR + w) * 512 + (e & 511)]);
           if (row < n) y[(int64_t)row * BW + (e & 15)] = o;
         }
       }
@@ -880,9 +914,10 @@ __global__ __launch_bounds__(64 * NW) void k_band_x(BandArgs a, BandFirst f, int
   const BandProb& p = a.p[pi];
   if (failed(p.info)) return;
   const int bx = (int)blockIdx.x - f.b[pi];
-  const int t = BW * (k + 1), n = p.n, m = n - t, ST = step_tile(m), nI = cdiv(m, ST);
+  const int t = BW * (k + 1), n = p.n, m = n - t;
+  const int RH = step_halves(m), rows = RH * step_tile(m), nI = cdiv(m, rows);
   const int G = gs.b[pi];  // blocks of this problem's k_band_step launch
-  const int64_t T = (int64_t)nI * (nI + 1) / 2, N16 = (int64_t)n * BW;
+  const int64_t T = (int64_t)RH * nI * (nI + 1) / 2, N16 = (int64_t)n * BW;
   __shared__ double2 xs[RB * LDT];
   __shared__ double2 red[NW * 256];
   __shared__ double2 sc[BW], cv[BW], Ts[256];
@@ -899,7 +934,7 @@ __global__ __launch_bounds__(64 * NW) void k_band_x(BandArgs a, BandFirst f, int
 #pragma unroll
   for (int c = 0; c < 4; ++c)
     vf[c] = V[(int64_t)min(t + bx * RB + wid * 16 + hi + 4 * c, n - 1) * BW + lo];
-  // the sums over the slots: column c of rows rr0 + 16 w, ST rows of a tile-row at
+  // the sums over the slots: column c of rows rr0 + 16 w, the rows of a tile-row at
   // a time (four rows per thread, eight slots of each in flight)
   {
     const int c = tid & 15, rr0 = tid >> 4;
@@ -912,9 +947,9 @@ __global__ __launch_bounds__(64 * NW) void k_band_x(BandArgs a, BandFirst f, int
     for (int q = 0; q < QR; ++q) {
       x[q] = czero();
       lr[q] = min(bx * RB + rr0 + RT * q, m - 1);
-      Ir[q] = lr[q] / ST;
-      const int64_t s0 = (int64_t)Ir[q] * (Ir[q] + 1) / 2;
-      nrs[q] = block_of(T, G, s0 + Ir[q]) - block_of(T, G, s0) + 1;
+      Ir[q] = lr[q] / rows;
+      const int64_t s0 = (int64_t)RH * Ir[q] * (Ir[q] + 1) / 2;
+      nrs[q] = block_of(T, G, s0 + RH * (Ir[q] + 1) - 1) - block_of(T, G, s0) + 1;
       tot[q] = nrs[q] + nI - Ir[q];
       most = max(most, tot[q]);
     }
@@ -1469,8 +1504,9 @@ int64_t ctl_elems(int64_t n) { return (((int64_t)band_ctl_ints((int)n) + 63) / 6
 // Blocks of a k_band_step launch over a trailing matrix of order m: up to eight
 // wavefronts per compute unit, two per SIMD.
 int step_grid(int64_t m) {
-  const int64_t st = step_tile(m), nI = (m + st - 1) / st, T = nI * (nI + 1) / 2;
-  return (int)std::max<int64_t>(1, std::min<int64_t>((128 / st) * device_cus(), T));
+  const int64_t rh = step_halves(m), rt = rh * step_tile(m);
+  const int64_t nI = (m + rt - 1) / rt, T = rh * nI * (nI + 1) / 2;
+  return (int)std::max<int64_t>(1, std::min<int64_t>((128 / rt) * device_cus(), T));
 }
 
 // Slots of k_band_step's partial products: two per tile-row, for the largest order
@@ -1547,15 +1583,18 @@ bool tridiagonalise_band(const BandItem* it_all, int np_all, hipStream_t s) {
       for (int q = 0; q < np; ++q) gs.b[q] = A.p[q].n > t ? step_grid(A.p[q].n - t) : 0;
       BAND_LAUNCH(k_band_chol, DIRECT_ROWS, k);
       BAND_LAUNCH(k_band_panel, 1, k);
-      for (int st : {32, 64}) {
-        const BandFirst fs = ranges(
-            [&](int64_t n) { return n > t && step_tile(n - t) == st ? step_grid(n - t) : 0; });
+      for (int rt : {32, 64, 128}) {
+        const BandFirst fs = ranges([&](int64_t n) {
+          return n > t && step_halves(n - t) * step_tile(n - t) == rt ? step_grid(n - t) : 0;
+        });
         const dim3 grid(fs.b[BAND_BATCH_MAX]);
         if (grid.x == 0) continue;
-        if (st == 32)
+        if (rt == 32)
           BSE_LAUNCH(k_band_step<32>, grid, dim3(128), 0, s, A, fs, k);
-        else
+        else if (rt == 64)
           BSE_LAUNCH(k_band_step<64>, grid, dim3(256), 0, s, A, fs, k);
+        else
+          BSE_LAUNCH(k_band_step<128>, grid, dim3(512), 0, s, A, fs, k);
       }
       BAND_LAUNCH(k_band_x, 1, k, gs);
       BAND_LAUNCH(k_band_w, 1, k);
