@@ -1388,16 +1388,13 @@ __global__ __launch_bounds__(CH_THREADS) void k_band_chase(BandArgs a, int np, i
     const int steps = n > 1 ? 2 * (slast - s0) + (n - 2 - slast) / BW + 2 : 0;
     const int dw = wid - CS, fw = wid - 2 * CS;  // diagonal; fetching (FW: storing)
     const int lw = fw - FW;
-    // step j takes columns s0 + 16 j + 1 .. + 16; s0 and those of step 0 first
+    // step j takes columns s0 + 16 j .. + 15 (its bulge reaches the first of them);
+    // those of step 0 first, those of step 1 put at step 0
     if (fw == 0 || fw == 1) {
       const int lane = opaque_lane();
-      wait_for(min(n, s0 + BW + 1));
-      fetch(lane, s0 + fw);
-      put(lane, s0 + fw);
-      if (fw == 1) {  // for step 1, put at step 0
-        wait_for(min(n, s0 + 2 * BW + 1));
-        fetch(lane, s0 + BW + 1);
-      }
+      wait_for(min(n, s0 + BW * (fw + 1)));
+      fetch(lane, s0 + BW * fw);
+      if (fw == 0) put(lane, s0);
     }
     __syncthreads();
     // the three kinds of wavefronts, each with one barrier per step
@@ -1428,13 +1425,19 @@ __global__ __launch_bounds__(CH_THREADS) void k_band_chase(BandArgs a, int np, i
         __syncthreads();
       }
     } else if (lw < 0) {
+      // the previous group's progress is asked for one step before it is needed: in a
+      // steady flow no step waits for a poll
       const int lane = opaque_lane();
+      int asked = seen;
       for (int i = 0; i < steps; ++i) {
         if ((i & 1) == fw) {  // request the columns of step i + 2
-          wait_for(min(n, s0 + BW * (i + 3) + 1));
-          fetch(lane, s0 + BW * (i + 2) + 1);
+          seen = max(seen, asked);
+          wait_for(min(n, s0 + BW * (i + 3)));
+          fetch(lane, s0 + BW * (i + 2));
         } else {
-          put(lane, s0 + BW * (i + 1) + 1);
+          put(lane, s0 + BW * (i + 1));
+          if (seen < n)
+            asked = __hip_atomic_load(prog + g - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
       }
