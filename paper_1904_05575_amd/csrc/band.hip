@@ -1194,6 +1194,10 @@ constexpr int BUFFER_FLAGS = 0x00027000;  // raw buffer, 32-bit data
 // lane's four values and the four lane groups.  (The rank-two updates on the matrix
 // cores, a 16 x 16 x 4 product each for the real and the imaginary part, take more
 // instructions to arrange than the vector ALU's 32.)
+// A group of CS sweeps follows the one before it by about ten steps of 1.2 us: n = 324,
+// 1875, 6144: 0.98, 6.3, 22.6 ms (1.09, 7.1, 26.6 ms when a group waited for 33 columns
+// in place of chunks of 16, polled within the step and gave both tasks the same
+// priority; CS = 2, 3, 5, 6 at n = 2048: 8.3, 8.2, 9.4, 9.1 ms against 7.8).
 
 // The block at rows r0 .. r0 + 15 and columns r0 - 16 .. r0 - 1 (first: the column
 // s alone), by one wavefront: the previous reflector from the right, B - z v^H; the
@@ -1417,6 +1421,7 @@ __global__ __launch_bounds__(CH_THREADS) void k_band_chase(BandArgs a, int np, i
       }
     } else if (fw < 0) {
       const int lane = opaque_lane(), lo = lane & 15, hi = lane >> 4;
+      __builtin_amdgcn_s_setprio(2);  // the longer of the two tasks of a step on its SIMD
       const int s = s0 + dw;
       for (int i = 0; i < steps; ++i) {
         const int k = i - 1 - 2 * dw, r0 = s + 1 + BW * k;
@@ -1424,6 +1429,7 @@ __global__ __launch_bounds__(CH_THREADS) void k_band_chase(BandArgs a, int np, i
           chase_diag(ring, ub[dw][(i & 1) ^ 1], ws[dw], lo, hi, r0);
         __syncthreads();
       }
+      __builtin_amdgcn_s_setprio(0);
     } else if (lw < 0) {
       // the previous group's progress is asked for one step before it is needed: in a
       // steady flow no step waits for a poll
