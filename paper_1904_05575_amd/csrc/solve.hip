@@ -150,7 +150,7 @@ namespace {
 // thread keeps two elements of the block and two of the identity, and a step's
 // pivot row and column go through LDS with one barrier.  (A forward substitution
 // of the columns, one per thread, would be a second chain as long: 37-40 us a
-// panel with it.)  Block 0 stores U11 into u11 (panel j0 / CH_NB holds CH_NB x
+// panel with it, 17 without.)  Block 0 stores U11 into u11 (panel j0 / CH_NB holds CH_NB x
 // CH_NB entries), not into A: the other blocks may still be reading A11 when
 // block 0 is done.  k_potrf_store moves every U11 into A once the factorisation is
 // complete.

@@ -203,8 +203,8 @@ int tile_edge(const ZgemmParams& p, int batch) {
 
 }  // namespace
 
-// The products are bound by the matrix cores (about 50 TFLOP/s of FP64 products is
-// what they sustain), so Gauss's three products in place of four are a quarter less
+// The products are bound by the matrix cores (about 50 TFLOP/s of FP64 products issued
+// in every form), so Gauss's three products in place of four are a quarter less
 // time where the third accumulator leaves enough wavefronts: 64-edge tiles take eight
 // wavefronts of 16 x 32 (48 accumulator registers).  At N = 6144, four products on four
 // wavefronts of 32 x 32 / three on the same / three on eight: U (A+B) 18.3 / 22.3 / 14.1
