@@ -46,6 +46,13 @@ namespace {
 constexpr int BW = BAND_W;
 static_assert(BW == 16, "one 16 x 16 matrix-core tile per block of the band");
 constexpr int DIRECT_ROWS = 64;   // panels with fewer rows are factored column by column
+// Elements of E = Q1^H Q1 - I (real and imaginary parts) up to which the second pass of a
+// panel takes its series: they bound ||E|| by 1.5 BW SERIES_MAX, and the series' errors, a
+// few ||E||^4, have to stay below rounding for the panel to be orthonormal to rounding.
+// (Well-conditioned panels have E near 1e-14; this limit is met from cond(P) ~ 1e5 on.)
+constexpr double SERIES_MAX = 2e-6;
+constexpr double fourth(double x) { return x * x * x * x; }
+static_assert(8 * fourth(1.5 * BW * SERIES_MAX) < 1.1e-16, "the series is exact to rounding");
 constexpr int LDT = BW + 1;       // padded row of a 16 x 16 tile in LDS
 constexpr int ABS = 2 * BW + 2;   // band storage per column: 2 BW diagonals, the probe, one spare
                                   // (in LDS a row of the band then steps by 2 BW + 1 values, over
@@ -579,11 +586,11 @@ __global__ __launch_bounds__(64 * NW) void k_band_panel(BandArgs a, BandFirst f,
     const double2 qt = p.Q1[(int64_t)(t + i) * BW + j];
     sum_partials<NW>(p.g2, panel_blocks(m), G, tmp);
     // R2 (in L) and its inverse (in Li), upper triangular, R2^H R2 = G = I + E.  For
-    // E below 1e-4 from the fixed point X = upper(E - X^H X) (diagonal halved) of R2
-    // = I + X, whose error goes from E^2 to E^3 and E^4, and 1 - X + X^2 - X^3:
-    // four products in place of sixteen dependent steps
+    // a small E from the fixed point X = upper(E - X^H X) (diagonal halved) of R2
+    // = I + X, whose error goes from ||E||^2 to ||E||^3 and ||E||^4, and 1 - X + X^2 -
+    // X^3: four products in place of sixteen dependent steps
     const double2 E = csub(G[e], make_double2(i == j ? 1.0 : 0.0, 0.0));
-    const bool tiny = __syncthreads_and(fabs(E.x) < 1e-4 && fabs(E.y) < 1e-4);
+    const bool tiny = __syncthreads_and(fabs(E.x) < SERIES_MAX && fabs(E.y) < SERIES_MAX);
     if (tiny) {
       const double half = i < j ? 1.0 : i == j ? 0.5 : 0.0;
       double2 x = cscale(E, half);
