@@ -150,7 +150,9 @@ namespace {
 // thread keeps two elements of the block and two of the identity, and a step's
 // pivot row and column go through LDS with one barrier.  (A forward substitution
 // of the columns, one per thread, would be a second chain as long: 37-40 us a
-// panel with it, 17 without.)  Block 0 stores U11 into u11 (panel j0 / CH_NB holds CH_NB x
+// panel with it, 17 without.)  The product with the explicit inverse leaves a residual
+// A12 - U11^H X of the order u cond(U11) ||A12||, so it is taken once more for that
+// residual, which leaves u ||A12|| as the substitution does.  Block 0 stores U11 into u11 (panel j0 / CH_NB holds CH_NB x
 // CH_NB entries), not into A: the other blocks may still be reading A11 when
 // block 0 is done.  k_potrf_store moves every U11 into A once the factorisation is
 // complete.
@@ -160,7 +162,8 @@ BSE_DEV void potrf_panel_dev(double2* __restrict__ A, int64_t ld, int64_t n, int
                              double2* __restrict__ u11, int32_t* info, int bx) {
   static_assert(CH_NB == 32 && PTHREADS == CH_NB * 16, "two elements per thread");
   __shared__ double2 ra[2][CH_NB], ry[2][CH_NB], ca[2][CH_NB];  // two steps' buffers
-  __shared__ double2 Li[CH_NB][CH_NB + 1];                      // U11^-H
+  __shared__ double2 Li[CH_NB][CH_NB + 1], L[CH_NB][CH_NB + 1];  // U11^-H, U11^H
+  __shared__ double2 xs[CH_NB][PCOLS];  // the panel row's first product, then its residual
   __shared__ double rs[CH_NB];                                  // 1 / U11[i][i]
   if (failed(info)) return;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
@@ -229,22 +232,38 @@ BSE_DEV void potrf_panel_dev(double2* __restrict__ A, int64_t ld, int64_t n, int
   for (int q = 0; q < 2; ++q) {
     const int j = (tid & 15) + 16 * q;
     Li[i][j] = i >= j ? cscale(y[q], rs[i]) : zero;
-    if (bx == 0 && i <= j && j < jb) {
-      const double2 u = cscale(v[q], rs[i]);
-      dst[i + j * CH_NB] = i == j ? make_double2(u.x, 0.0) : u;
-    }
+    double2 u = cscale(v[q], rs[i]);
+    if (i == j) u.y = 0.0;
+    L[j][i] = i <= j ? cconj(u) : zero;
+    if (bx == 0 && i <= j && j < jb) dst[i + j * CH_NB] = u;
   }
   if (jb != CH_NB) return;  // the last panel has no panel row
   // the tile's loads are complete before another wavefront stores over them
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  Acc acc;
+  Acc acc, back, fix;
+  const int xc = (wid & 3) * 16 + lo;  // this lane's column of xs
 #pragma unroll
   for (int k = 0; k < 8; ++k)
     if (k < 4 || rt) acc.mac(Li[16 * rt + lo][hi + 4 * k], x[k]);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) xs[16 * rt + hi + 4 * r][xc] = acc.at(r);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (k < 4 || rt) back.mac(L[16 * rt + lo][hi + 4 * k], xs[hi + 4 * k][xc]);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    xs[16 * rt + hi + 4 * r][xc] = csub(rt ? x[4 + r] : x[r], back.at(r));
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (k < 4 || rt) fix.mac(Li[16 * rt + lo][hi + 4 * k], xs[hi + 4 * k][xc]);
   if (solve)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) A[(int64_t)(j0 + 16 * rt + hi + 4 * r) + c * ld] = acc.at(r);
+    for (int r = 0; r < 4; ++r)
+      A[(int64_t)(j0 + 16 * rt + hi + 4 * r) + c * ld] = cadd(acc.at(r), fix.at(r));
 }
 
 __global__ __launch_bounds__(PTHREADS) void k_potrf_panel(double2* __restrict__ A, int64_t ld,
