@@ -397,9 +397,9 @@ int64_t bse_timing_report(char* buf, int64_t len);
  *                          rows and at most 16 columns per pair block; else 7)
  *   BSE_TUNE_GEMM_PRODUCTS size = the larger output dimension of a complex GEMM;
  *                          choice = real matrix-core products per complex one
- *                          on 16- and 32-edge tiles: 4 (re = ar br - ai bi,
- *                          im = ar bi + ai br) or 3 (Gauss: ar br, ai bi,
- *                          (ar + ai)(br + bi)); 64-edge tiles always take 3
+ *                          on every tile edge: 4 (re = ar br - ai bi, im =
+ *                          ar bi + ai br) or 3 (default; Gauss: ar br, ai bi,
+ *                          (ar + ai)(br + bi))
  *   BSE_TUNE_BATCH_SWEEP, BSE_TUNE_BATCH_ALIGN  of an earlier batched
  *                          reduction: choices 0, 1, 2 or 4 and 0 or 1 are
  *                          accepted and have no effect

@@ -210,7 +210,10 @@ int tile_edge(const ZgemmParams& p, int batch) {
 // wavefronts of 32 x 32 / three on the same / three on eight: U (A+B) 18.3 / 22.3 / 14.1
 // ms, its product with U^H 6.1 / 7.3 / 4.6 ms, the Cholesky updates 9.9 / 12.8 / 7.3 ms
 // (N = 2000: 0.76 / 0.85 / 0.55, 0.49 / 0.39 / 0.32, 0.59 / 0.65 / 0.52 ms); tiles of
-// 128 x 64 and 128 x 128 gain nothing on that.
+// 128 x 64 and 128 x 128 gain nothing on that.  The energies of full problems of N = 700,
+// 1500 and 1900 (three of each) through 64-edge tiles are 16.7 (rms, in relative u) from 64
+// bits with three products and 17.0 with four; element by element three products are off by
+// u |a| |b| where four keep Re and Im apart, so four stay a choice on every edge.
 // Each item takes the tile edge and the products per complex one that zgemm()
 // would take for it alone, so that its values are those of that call; items
 // sharing both go into one launch.
@@ -226,7 +229,7 @@ hipError_t zgemm_group(const ZgemmParams& base, const ZgemmItem* items, int coun
                                     : tune_choice(BSE_TUNE_GEMM_PRODUCTS,
                                                   std::max(one.M, one.N), 3);
     const int edge = tile_edge(one, 1);
-    key[i] = edge * 8 + (edge == 64 ? 3 : prods);
+    key[i] = edge * 8 + prods;
   }
   std::vector<char> done(count, 0);
   for (int i = 0; i < count; ++i) {
@@ -252,8 +255,11 @@ hipError_t zgemm_group(const ZgemmParams& base, const ZgemmItem* items, int coun
       case 32 * 8 + 4:
         e = launch_group<32, 32, 2, 2, false>(base, g, ng, s);
         break;
-      default:
+      case 64 * 8 + 3:
         e = launch_group<64, 64, 4, 2, true>(base, g, ng, s);
+        break;
+      default:
+        e = launch_group<64, 64, 4, 2, false>(base, g, ng, s);
     }
     if (e != hipSuccess) return e;  // items of this key past the first launch: later in the loop
   }
@@ -272,6 +278,7 @@ hipError_t zgemm(const ZgemmParams& p, int batch, hipStream_t s) {
       return prods == 3 ? launch<32, 32, 2, 2, true>(p, batch, s)
                         : launch<32, 32, 2, 2, false>(p, batch, s);
     default:
-      return launch<64, 64, 4, 2, true>(p, batch, s);
+      return prods == 3 ? launch<64, 64, 4, 2, true>(p, batch, s)
+                        : launch<64, 64, 4, 2, false>(p, batch, s);
   }
 }
