@@ -1657,5 +1657,6 @@ int64_t band_big_bytes(int64_t n) {
   return 16 * (band_elems(n) + ctl_elems(n) + slots);
 }
 int64_t band_part_bytes(int64_t n) {
+  if (n <= BW) return 0;  // no panel
   return 16 * (((n + 63) / 64) * (3 * 256 + BW) + 512);
 }

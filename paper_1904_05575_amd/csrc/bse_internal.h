@@ -112,6 +112,9 @@ CholItem solve_chol_item(const bse_desc* d, void* H1, void* ws, int32_t* info);
 // them; `project`: spectrum-only run with a probe).
 struct BandItem;
 BandItem solve_sweep_item(const bse_desc* d, void* H0, void* ws, bool project, int32_t* info);
+// Whether what that item borrows from the workspace holds what the reduction writes there
+// (true by construction; checked on the host by the tests).
+bool solve_band_fits(const bse_desc* d);
 
 // screening.hip
 size_t screening_workspace(const bse_screen_desc* d);

@@ -1217,14 +1217,19 @@ SolveWs carve(const bse_desc* d, void* base) {
   const int64_t npnl = (n + TRD_NB - 1) / TRD_NB + 1;
   WsLayout L(base);
   SolveWs w;
+  // the band reduction of solves without eigenvectors borrows Wk .. Dm, one span, and
+  // W1, W2, VW (solve_sweep_item): each at least as large as it needs
+  static_assert(4 * BAND_W <= 2 * TRD_NB && 2 * BAND_W <= TRD_NB, "VW and W2 serve both");
   w.Wk = (double2*)L.add(n * n * 16);
+  const int64_t wk = (int64_t)L.total - n * n * 16;
   w.Ztri = (double*)L.add(n * n * 8);
   w.Dp = (double*)L.add(n * (n + EV_JUNK) * 8);
-  w.Dm = (double*)L.add(n * (n + EV_JUNK) * 8);
+  const int64_t dm = ((int64_t)L.total + 255) & ~(int64_t)255;
+  w.Dm = (double*)L.add(std::max(n * (n + EV_JUNK) * 8, wk + band_big_bytes(n) - dm));
   w.VW = (double2*)L.add(n * 2 * TRD_NB * 16);
   w.WV = (double2*)L.add(n * 2 * TRD_NB * 16);
   static_assert(CH_NB <= TRD_NB, "the U11 blocks fit in W1");
-  w.W1 = (double2*)L.add((n + CH_NB) * TRD_NB * 16);
+  w.W1 = (double2*)L.add(std::max((n + CH_NB) * TRD_NB * 16, band_part_bytes(n)));
   w.W2 = (double2*)L.add(n * TRD_NB * 16);
   w.ybuf = (double2*)L.add(n * 16);
   w.yvec = (double2*)L.add(n * 16);
@@ -1791,6 +1796,15 @@ BandItem solve_sweep_item(const bse_desc* d, void* H0, void* ws, bool project, i
   it.b = BandBufs{w.VW, w.W2, w.W1, w.Wk, w.dd, w.ee, project ? w.yvec : nullptr};
   it.info = info;
   return it;
+}
+
+bool solve_band_fits(const bse_desc* d) {
+  const SolveWs w = carve(d, (void*)256);
+  const int64_t n = (int64_t)d->nk * d->nv * d->nc;
+  return (char*)w.VW - (char*)w.Wk >= band_big_bytes(n) &&
+         (char*)w.W2 - (char*)w.W1 >= band_part_bytes(n) &&
+         (char*)w.ybuf - (char*)w.W2 >= n * 2 * BAND_W * 16 &&
+         (char*)w.WV - (char*)w.VW >= n * 4 * BAND_W * 16;
 }
 
 CholItem solve_chol_item(const bse_desc* d, void* H1, void* ws, int32_t* info) {
