@@ -25,8 +25,8 @@
 //                 Gram partials of the next panel
 // Panels whose Gram matrix is not safely positive definite (columns that are
 // dependent, or fewer rows than the factorisation needs) take Householder's
-// column-by-column factorisation in one block of k_band_panel; panels that are
-// zero take H = I.
+// column-by-column factorisation in one block of k_band_panel, over the rows before
+// the part that is zero in every column; panels that are zero take H = I.
 //
 // Stage 2: k_band_chase (below).
 //
@@ -345,13 +345,14 @@ __global__ __launch_bounds__(64 * NW) void k_band_chol(BandArgs a, BandFirst f, 
 }
 
 // ------------------------------------------------ column-by-column panel
-// Panels of at most 64 rows, in registers of the block's first 256 threads:
+// Panels whose rows past the first m <= 64 are zero, in registers of the block's first 256 threads:
 // thread (c, l) holds rows l + 16 q of column c, so a sum over rows is one over
 // the 16 lanes of a DPP row; one barrier per column.  xcol: 2 x 64 values, gv: 2 x
 // BW, Tl: BW x LDT (LDS).  Columns already reduced hold their reflector, whose
 // product with the new one gives T's next column.
-BSE_DEV void panel_small(const BandProb& p, int k, double2* xcol, double2* gv, double2* Tl) {
-  const int j0 = BW * k, t = j0 + BW, n = p.n, m = n - t;
+BSE_DEV void panel_small(const BandProb& p, int k, int m, double2* xcol, double2* gv,
+                         double2* Tl) {
+  const int j0 = BW * k, t = j0 + BW, n = p.n;
   const int tid = threadIdx.x, l = tid & 15, c = tid >> 4;
   const bool on = tid < 256;
   double2* V = v_of(p, k);
@@ -449,13 +450,15 @@ BSE_DEV void panel_small(const BandProb& p, int k, double2* xcol, double2* gv, d
   if (on) p.sm[tid] = Tl[c * LDT + l];
 }
 
-// Householder factorisation of P = S[t:, j0:j0+BW] by one block, in place
-// (row i <= column j of the result is R), V and T as the fast path leaves them.
+// Householder factorisation of P = S[t:t+m, j0:j0+BW], the rows past m zero, by one
+// block, in place (row i <= column j of the result is R); the first m rows of V, and T,
+// as the fast path leaves them.
 // sums: NW * BW values, sv: BW values (LDS); Tl: BW * LDT (LDS).
 template <int NW>
-BSE_DEV void panel_direct(const BandProb& p, int k, double2* sums, double2* sv, double2* Tl) {
+BSE_DEV void panel_direct(const BandProb& p, int k, int m, double2* sums, double2* sv,
+                          double2* Tl) {
   constexpr int NT = 64 * NW;
-  const int j0 = BW * k, t = j0 + BW, n = p.n, m = n - t;
+  const int j0 = BW * k, t = j0 + BW;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   double2* V = v_of(p, k);
   double2* P = p.M + t + (int64_t)j0 * p.ld;
@@ -540,7 +543,7 @@ BSE_DEV void panel_direct(const BandProb& p, int k, double2* sums, double2* sv, 
     __syncthreads();
   }
   if (tid < 256) p.sm[tid] = Tl[(tid >> 4) * LDT + (tid & 15)];
-  if (p.yp) {  // V^H y into the first block's partial, the others cleared
+  if (p.yp) {  // V^H y, into the first block's partial
     double2 s[BW];
 #pragma unroll
     for (int c = 0; c < BW; ++c) s[c] = czero();
@@ -550,9 +553,24 @@ BSE_DEV void panel_direct(const BandProb& p, int k, double2* sums, double2* sv, 
       for (int c = 0; c < BW; ++c) s[c] = cadd(s[c], cmulc(V[(int64_t)(t + r) * BW + c], y));
     }
     block_sums(s);
-    const int nb = panel_blocks(m);
-    for (int e = tid; e < nb * BW; e += NT) p.pd[e] = e < BW ? sv[e] : czero();
+    if (tid < BW) p.pd[tid] = sv[tid];
   }
+}
+
+// Rows of the panel before the part that is zero in all its columns, from the Gram
+// partials of its row blocks (k_band_w's, over rows j0 ..): matrices that fall into blocks
+// or bands have few, wherever their columns are dependent.
+BSE_DEV int panel_extent(const BandProb& p, int j0, int* last) {
+  const int mw = p.n - j0;
+  if (threadIdx.x == 0) *last = 0;
+  __syncthreads();
+  for (int b = threadIdx.x; b < panel_blocks(mw); b += blockDim.x) {
+    bool some = false;
+    for (int s = 0; s < BW; ++s) some = some || p.g1[(int64_t)b * 256 + 17 * s].x != 0.0;
+    if (some) atomicMax(last, b);
+  }
+  __syncthreads();
+  return min((*last + 1) * panel_rows(mw), mw) - BW;
 }
 
 // ------------------------------------------------------ panel, second pass
@@ -569,10 +587,11 @@ __global__ __launch_bounds__(64 * NW) void k_band_panel(BandArgs a, BandFirst f,
   __shared__ double2 Dv[BW];
   __shared__ double dg[BW];
   __shared__ StepShare sh;
+  __shared__ int last;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, lo = lane & 15, hi = lane >> 4;
   double2* V = v_of(p, k);
   if (m < DIRECT_ROWS) {  // uniform; one block
-    panel_small(p, k, red, G, L);
+    panel_small(p, k, m, red, G, L);
     return;
   }
   const int row = t + bx * RB + wid * 16 + lo;
@@ -682,17 +701,23 @@ __global__ __launch_bounds__(64 * NW) void k_band_panel(BandArgs a, BandFirst f,
     // an inverse far above the order of 1 would cost H its unitarity
     if (!__syncthreads_and(fabs(y.x) < 1e3 && fabs(y.y) < 1e3)) state = 1;
   }
-  if (state == 1) {
-    if (bx == 0) panel_direct<NW>(p, k, red, G, L);
-    return;
-  }
-  if (state == 2) {  // H = I
-    if (row < n) {
+  if (state != 0) {
+    // 1: column by column, by the first block; 2: H = I.  V and its probe partials are
+    // cleared where that leaves them
+    const int me = state == 1 ? panel_extent(p, j0, &last) : 0;
+    if (row < n && row - t >= me) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) V[(int64_t)row * BW + hi + 4 * r] = czero();
     }
-    if (tid < BW) p.pd[(int64_t)bx * BW + tid] = czero();
-    if (bx == 0 && on) p.sm[tid] = czero();
+    if ((bx > 0 || state == 2) && tid < BW) p.pd[(int64_t)bx * BW + tid] = czero();
+    if (bx > 0) return;
+    if (state == 2) {
+      if (on) p.sm[tid] = czero();
+    } else if (me <= 64) {
+      panel_small(p, k, me, red, G, L);
+    } else {
+      panel_direct<NW>(p, k, me, red, G, L);
+    }
     return;
   }
   if (bx == 0 && on) {  // T = -D^* (Q_top - D)^-H and R = D R2 R1
