@@ -18,8 +18,8 @@ namespace {
 // lanes of a wavefront hold 64 columns (k', n) of one k, staged in LDS as [K'][column],
 // a K outside the sphere is skipped, the partner's row is one conflict-free 16-byte
 // read per lane, and conj(C_m,k(K)) comes through the scalar cache for na <= 5 bands
-// m: 4 na FMA instructions per read.  Four G are summed one after the other and
-// stored together, 64 consecutive bytes per element.
+// m: 4 na FMA instructions per read.  Four G (two on small meshes) are summed one after
+// the other and stored together, 64 consecutive bytes per element.
 // 23436 pairs of 4 + 5 bands, 89 G and 89 K (45 % of them inside the sphere): 2.15 ms,
 // the vector ALU busy for 68 % of it, 2.7 GB written; a lane per G with blocks padded
 // to 4 x 4 bands, both operands gathered from LDS, took 4.4 ms, and 8 k' x 8 G per
@@ -28,7 +28,7 @@ constexpr int PG_WAVES = 16;  // four wavefronts per SIMD, one block per compute
 constexpr int PG_THREADS = 64 * PG_WAVES;
 constexpr int PG_MAXB = 5;    // bands of a block at k, of a side at k'
 constexpr int PG_ROWS = 128;  // rows K' in LDS at a time
-constexpr int PG_BATCH = 4;   // G of a task
+constexpr int PG_BATCH = 4;   // G of a task: 4 or 2
 constexpr int PG_TR = 128;    // values of a wavefront's transposition buffer
 constexpr int PG_MAXKINDS = 24;
 constexpr int PG_LDS = 160 * 1024;
@@ -72,13 +72,13 @@ BSE_DEV void stage_rows(double2* ys, const double2* __restrict__ C, const PgCols
   }
 }
 
-// One task: NA bands at k (uniform, xs: C_m,k) with the 64 columns, for the G from g0.
+// One task: NA bands at k (uniform, xs: C_m,k) with the 64 columns, for NQ G from g0.
 // nch > 1: the rows K' come in parts, staged by the whole block; all its wavefronts call
 // with the same kind, those past the last G with none to sum.
-template <int NA, bool MOD, class Stage>
+template <int NQ, int NA, bool MOD, class Stage>
 BSE_DEV void pair_task(const double2* __restrict__ xs, int nkb, const double2* ys,
                        const int32_t* __restrict__ tab, int ng, int g0, int nch, Stage stage,
-                       double2* tr, const int (&pcol)[4], const PgKind& kd, int64_t pair0, int ik) {
+                       double2* tr, const int (&pcol)[NQ], const PgKind& kd, int64_t pair0, int ik) {
   const int lane = threadIdx.x & 63;
   uint32_t xa[NA];  // bands of one k-point: at most 80 KB
 #pragma unroll
@@ -86,21 +86,21 @@ BSE_DEV void pair_task(const double2* __restrict__ xs, int nkb, const double2* y
     xa[a] = (uint32_t)(a * nkb) * (uint32_t)sizeof(double2);
     asm("" : "+s"(xa[a]));  // one sum per load, not a chain of 64-bit ones
   }
-  double2 acc[PG_BATCH][NA];
+  double2 acc[NQ][NA];
 #pragma unroll
-  for (int q = 0; q < PG_BATCH; ++q)
+  for (int q = 0; q < NQ; ++q)
 #pragma unroll
     for (int a = 0; a < NA; ++a) acc[q][a] = make_double2(0.0, 0.0);
   for (int ch = 0; ch < nch; ++ch) {
     const int r0 = ch * PG_ROWS, rows = min(PG_ROWS, nkb - r0);
     if (nch > 1) stage(r0, rows);
     for (int K0 = 0; K0 < nkb; K0 += 64) {
-      int row[PG_BATCH];  // lane: the partner row of K0 + lane
+      int row[NQ];  // lane: the partner row of K0 + lane
 #pragma unroll
-      for (int q = 0; q < PG_BATCH; ++q)
+      for (int q = 0; q < NQ; ++q)
         row[q] = tab[(int64_t)min(K0 + lane, nkb - 1) * ng + min(g0 + q, ng - 1)] - r0;
 #pragma unroll
-      for (int q = 0; q < PG_BATCH; ++q) {
+      for (int q = 0; q < NQ; ++q) {
         uint64_t mask = __ballot(g0 + q < ng && K0 + lane < nkb && (unsigned)row[q] < (unsigned)rows);
         auto take = [&](double2 (&x)[NA], double2& y) __attribute__((always_inline)) {
           const int K = (int)__builtin_ctzll(mask);
@@ -140,21 +140,21 @@ BSE_DEV void pair_task(const double2* __restrict__ xs, int nkb, const double2* y
     }
   }
   // through LDS, 32 columns at a time, into lanes with G fastest
-  const int cl = lane & 31, sw = (cl >> 1) & 3;
+  const int cl = lane & 31, sw = (cl >> 1) & (NQ - 1);
 #pragma unroll
   for (int a = 0; a < NA; ++a)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       if (lane >> 5 == h) {
 #pragma unroll
-        for (int q = 0; q < PG_BATCH; ++q)
-          tr[cl * 4 + (q ^ sw)] = make_double2(acc[q][a].x, MOD ? -acc[q][a].y : acc[q][a].y);
+        for (int q = 0; q < NQ; ++q)
+          tr[cl * NQ + (q ^ sw)] = make_double2(acc[q][a].x, MOD ? -acc[q][a].y : acc[q][a].y);
       }
       wave_lds_sync();
 #pragma unroll
-      for (int v = 0; v < 2; ++v) {
-        const int e = lane + 64 * v, c = e >> 2, g = g0 + (e & 3), pc = pcol[2 * h + v];
-        const double2 z = tr[c * 4 + ((e & 3) ^ ((c >> 1) & 3))];
+      for (int v = 0; v < NQ / 2; ++v) {
+        const int e = lane + 64 * v, c = e / NQ, g = g0 + e % NQ, pc = pcol[h * (NQ / 2) + v];
+        const double2 z = tr[c * NQ + (e % NQ ^ ((c >> 1) & (NQ - 1)))];
         const int jk = pc >> 3;
         if (pc >= 0 && g < ng && (!kd.diag_only || jk == ik))
           kd.out[(kd.diag_only ? ik : pair0 + jk) * kd.ps + (kd.ia + a) * kd.as +
@@ -164,6 +164,7 @@ BSE_DEV void pair_task(const double2* __restrict__ xs, int nkb, const double2* y
     }
 }
 
+template <int NQ>
 __global__ __launch_bounds__(PG_THREADS) void k_pair_elements(
     const double2* __restrict__ C, int nk, int nbt, int nkb, int ng,
     const int32_t* __restrict__ kpg, const int32_t* __restrict__ mkg, PgKinds kinds) {
@@ -190,10 +191,10 @@ __global__ __launch_bounds__(PG_THREADS) void k_pair_elements(
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rows0 = min(nkb, PG_ROWS), nch = (nkb + PG_ROWS - 1) / PG_ROWS;
   double2* tr = ys + rows0 * 64 + PG_TR * wid;
-  int pcol[4];  // the columns this lane stores: k' << 3 | n
+  int pcol[NQ];  // the columns this lane stores: k' << 3 | n
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int c = cols.c0 + 16 * v + (lane >> 2), jk = cols.jk(c);
+  for (int v = 0; v < NQ; ++v) {
+    const int c = cols.c0 + 64 / NQ * v + lane / NQ, jk = cols.jk(c);
     pcol[v] = c < cols.total ? jk << 3 | (c - (jk - ik) * cols.nb) : -1;
   }
   const int64_t pair0 = (int64_t)ik * nk - (int64_t)ik * (ik - 1) / 2 - ik;  // + jk: the pair
@@ -204,19 +205,19 @@ __global__ __launch_bounds__(PG_THREADS) void k_pair_elements(
   };
   if (nch == 1) stage(0, nkb);
   const int nkinds = sd.count - (cg == 0 ? 0 : sd.diag);
-  const int ngb = (ng + PG_BATCH - 1) / PG_BATCH;
+  const int ngb = (ng + NQ - 1) / NQ;
   // rows in one part: the tasks of all kinds over the wavefronts; in several: kind by
   // kind, the block's wavefronts together
   const int step = PG_WAVES * (int)gridDim.z, t0 = wid + PG_WAVES * (int)blockIdx.z;
   const int per = nch == 1 ? ngb : (ngb + step - 1) / step * step;
   for (int t = t0; t < nkinds * per; t += step) {
     const PgKind& kd = kinds.k[sd.first + t / per];
-    const int g0 = (t % per) * PG_BATCH;
+    const int g0 = (t % per) * NQ;
     const int32_t* tab = kd.modified ? mkg : kpg;
     const double2* xs = C + ((int64_t)ik * nbt + kd.a0) * nkb;
 #define PAIR_CASE(A, M)                                                                         \
   case M * 8 + A:                                                                               \
-    pair_task<A, M>(xs, nkb, ys, tab, ng, g0, nch, stage, tr, pcol, kd, pair0, ik);             \
+    pair_task<NQ, A, M>(xs, nkb, ys, tab, ng, g0, nch, stage, tr, pcol, kd, pair0, ik);             \
     break;
     switch (kd.modified * 8 + kd.na) {
       PAIR_CASE(1, 0) PAIR_CASE(2, 0) PAIR_CASE(3, 0) PAIR_CASE(4, 0) PAIR_CASE(5, 0)
@@ -246,6 +247,48 @@ void add_kinds(PgKinds& ks, double2* out, int64_t ps, int64_t as, int64_t bs, in
     k.nb = nb;
     k.modified = modified;
     k.diag_only = diag_only;
+  }
+}
+
+// G per task (4 or 2) and blocks per 64 columns (grid.z).  A block's time, in units of one
+// G's pass over K: its rounds of one task per wavefront, each as long as its G and 0.7,
+// and 0.6 + 100 / N_K for its start and the rows it stages.  One block per compute unit;
+// beyond 256 of them they queue.  So few blocks (small meshes) are split until every
+// wavefront has one short task, a number a little above 256 so that no unit is left with a
+// whole block more than the others, and large meshes take long tasks, whose stores are
+// wider.  us of 4 G and one block per 64 columns against the choice (k-points, bands, N_G,
+// N_K): 1, 4 + 4, 59, 59: 74 / 21 (2 G, 6 blocks); 27, 2 + 2, 51, 89: 77 / 24 (2 G, 5);
+// 27, 3 + 4, 27, 27: 24.8 / 15.3 (2 G, 3); 64, 3 + 4, 113, 113: 403 / 314 (4 G, 2); 64,
+// 3 + 4, 113, 169: 707 / 531 (4 G, 2); 125, 4 + 5, 59, 113: 739 with 4 G and one block, 837
+// with two.  (Two G as a kernel of their own: half the code and no spilled registers,
+// 20.0 -> 15.3 us at the third against a bound on G in the other.)
+void pair_split(const PgKinds& ks, int nk, int ng, int nkb, int& nq, int& split) {
+  const int nch = (nkb + PG_ROWS - 1) / PG_ROWS;
+  double blocks = 0.0;  // of 64 columns, over the rows of k-points
+  int most = 0, off_diag = 0;  // kinds of a block with diagonal pairs, of the others
+  for (int i = 0; i < ks.nsides; ++i) {
+    const PgSide& sd = ks.side[i];
+    blocks += sd.nb * (double)nk * (nk + 1) / 128.0 + 0.5 * nk;
+    most = std::max(most, sd.count);
+    off_diag = std::max(off_diag, sd.count - sd.diag);
+  }
+  double best = 0.0;
+  nq = PG_BATCH;
+  split = 1;
+  for (int q = PG_BATCH; q >= 2; q /= 2) {
+    const int ngb = (ng + q - 1) / q;
+    const int zmax = std::min(cdiv(nch > 1 ? ngb : most * ngb, PG_WAVES), 16);
+    for (int z = 1; z <= zmax; ++z) {
+      const int kinds = blocks * z <= 256.0 ? most : off_diag;
+      const double t = nch > 1 ? kinds * cdiv(ngb, PG_WAVES * z) * (q + 0.7 + 0.6 * nch)
+                               : cdiv(kinds * ngb, PG_WAVES * z) * (q + 0.7) + 0.6 + 100.0 / nkb;
+      const double cost = t * std::max(1.0, blocks * z / 256.0 + 0.25);
+      if (best == 0.0 || cost < 0.98 * best) {
+        best = cost;
+        nq = q;
+        split = z;
+      }
+    }
   }
 }
 
@@ -295,17 +338,20 @@ bse_status bse_pair_elements(const bse_orb_desc* d, const void* C, const int32_t
   }
   const size_t lds = ((size_t)std::min(nkb, PG_ROWS) * 64 + PG_TR * PG_WAVES) * sizeof(double2);
   const int64_t groups = (int64_t)((d->nk + 1) / 2) * row_groups(d->nk, nbmax);
-  // a few k-points: their G over several blocks, one block per compute unit
-  const int64_t tasks = (full ? 2 : 1) * cdiv(ng, PG_BATCH);
-  const int64_t split = std::max<int64_t>(
-      1, std::min<int64_t>(cdiv(tasks, PG_WAVES), 256 / (groups * ks.nsides)));
-  if (lds > 64 * 1024 &&
-      hipFuncSetAttribute((const void*)k_pair_elements,
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-    return BSE_ERR_HIP;
-  BSE_LAUNCH(k_pair_elements, dim3((unsigned)groups, (unsigned)ks.nsides, (unsigned)split),
-             dim3(PG_THREADS), lds, stream, (const double2*)C, d->nk, nbt, nkb, ng, kpg,
-             full ? mkg : kpg, ks);
+  int nq, split;
+  pair_split(ks, d->nk, ng, nkb, nq, split);
+  // (the parameter has the kernel's name, under which the launch is timed)
+  auto launch = [&](auto* k_pair_elements) {
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute((const void*)k_pair_elements, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds) != hipSuccess)
+      return false;
+    BSE_LAUNCH(k_pair_elements, dim3((unsigned)groups, (unsigned)ks.nsides, (unsigned)split),
+               dim3(PG_THREADS), lds, stream, (const double2*)C, d->nk, nbt, nkb, ng, kpg,
+               full ? mkg : kpg, ks);
+    return true;
+  };
+  if (!(nq == 4 ? launch(k_pair_elements<4>) : launch(k_pair_elements<2>))) return BSE_ERR_HIP;
   return hipGetLastError() == hipSuccess ? BSE_OK : BSE_ERR_HIP;
 }
 
