@@ -1,7 +1,7 @@
 """Autotuner of the library's tile choices (run on the GPU; writes a JSON table).
 
     python -m paper_1904_05575_amd.tune [--out PATH] [--reps 2]
-                                        [--hemv-only | --gemm-site SITE]
+                                        [--hemv-only | --gemm-site SITE | --batch-sweep-only]
 
 For every tunable call site of the FP64 path (see bse_tune_entry in
 include/bse.h) the tuner builds and solves seeded synthetic problems of the
@@ -126,6 +126,16 @@ def run_hemv_only(out: str, reps: int = 2) -> dict:
     return tab
 
 
+def run_batch_sweep_only(out: str, reps: int = 2) -> dict:
+    """The stored table, as it is, to `out`: the batched reduction has no choices left
+    (entries of the sites batch_sweep and batch_align are accepted without effect)."""
+    with open(TABLE) as f:
+        tab = json.load(f)
+    with open(out, "w") as f:
+        json.dump(tab, f, indent=1)
+    return tab
+
+
 def run_gemm_site_only(out: str, site: str, reps: int = 2) -> dict:
     """Re-tune one GEMM site on every problem order, keeping the table's other
     entries (installed while the site's choices are timed)."""
@@ -227,9 +237,14 @@ def main() -> int:
                     help="re-tune the hemv buckets only, keeping the other entries")
     ap.add_argument("--gemm-site", choices=sorted(GEMM_SITES),
                     help="re-tune one GEMM site only, keeping the other entries")
+    ap.add_argument("--batch-sweep-only", action="store_true",
+                    help="accepted without effect: the batched reduction has no choices left; "
+                         "the stored table is written as it is")
     args = ap.parse_args()
     if args.hemv_only:
         tab = run_hemv_only(args.out, args.reps)
+    elif args.batch_sweep_only:
+        tab = run_batch_sweep_only(args.out, args.reps)
     elif args.gemm_site:
         tab = run_gemm_site_only(args.out, args.gemm_site, args.reps)
     else:
