@@ -276,8 +276,8 @@ typedef struct {
  * kpg, mkg: int32 [nkb][ng], position in the sphere of K + G and of -K - G
  * (-1 when outside; mkg may be NULL in the TDA); outputs: device arrays in the
  * layouts of bse_inputs (Ncv, Nvc may be NULL in the TDA).  BSE_ERR_ARG for
- * a bad descriptor, a NULL pointer, or 2 (nv + nc) nkb coefficients beyond
- * 160 KB of LDS. */
+ * a bad descriptor, a NULL pointer, 2 (nv + nc) nkb coefficients beyond
+ * 160 KB, or more than 24 blocks of 4 x 4 bands over the element arrays. */
 bse_status bse_pair_elements(const bse_orb_desc* desc, const void* C, const int32_t* kpg,
                              const int32_t* mkg, void* Mcv, void* Mvv, void* Mcc, void* Ncv,
                              void* Nvc, hipStream_t stream);

@@ -4,10 +4,16 @@
 // reflectors, whose work is matrix products, then the band to tridiagonal form
 // by chasing bulges down the band.  The one-stage sweep (hetrd.hip) reads the
 // trailing triangle once per column; here it is read and written once per BW
-// columns, in a kernel that is bound by the matrix cores and not by memory.
-// n = 6144 (one-stage sweep: 190 ms, 618 GB of triangle reads): k_band_step 31.5 ms (38
-// TFLOP/s of products), k_band_x 8.1, k_band_panel 6.7, k_band_w 4.4, k_band_chol 4.2,
-// k_band_chase 22.9.  The panel kernels are chains: 10 to 19 us per launch at any order.
+// columns, in a kernel that works on the matrix cores.
+// n = 6144 (one-stage sweep: 190 ms, 618 GB of triangle reads): k_band_step 31.7 ms (29
+// TFLOP/s issued, in three real products per complex one: neither the matrix cores nor
+// memory bound it), k_band_x 8.1, k_band_panel 6.8, k_band_chol 4.6, k_band_w 4.4,
+// k_band_chase 22.6.  The panel kernels are chains: 10 to 19 us per launch at any order.
+//
+// The parts are published methods: QR by two Cholesky passes (Yamamoto, Nakatsukasa,
+// Yanagisawa and Fukaya, ETNA 44, 2015), the reflector form rebuilt from Q (Ballard,
+// Demmel, Grigori, Jacquelin, Nguyen and Solomonik, IPDPS 2014), the chase (Schwarz,
+// Numer. Math. 12, 1968; Lang, SIAM J. Sci. Comput. 14, 1993).
 //
 // Stage 1, panel k (columns j0 = BW k .., trailing rows and columns t = j0 + BW ..):
 //   k_band_chol   R1 from the Gram matrix of the panel P = S[t:, j0:j0+BW]
@@ -1251,9 +1257,10 @@ constexpr int BUFFER_FLAGS = 0x00027000;  // raw buffer, 32-bit data
 // cores, a 16 x 16 x 4 product each for the real and the imaginary part, take more
 // instructions to arrange than the vector ALU's 32.)
 // A group of CS sweeps follows the one before it by about ten steps of 1.2 us: n = 324,
-// 1875, 6144: 0.98, 6.3, 22.6 ms (1.09, 7.1, 26.6 ms when a group waited for 33 columns
+// 1875, 6144: 0.97, 6.3, 22.6 ms (1.09, 7.1, 26.6 ms when a group waited for 33 columns
 // in place of chunks of 16, polled within the step and gave both tasks the same
-// priority; CS = 2, 3, 5, 6 at n = 2048: 8.3, 8.2, 9.4, 9.1 ms against 7.8).
+// priority).  CS = 2, 3, 5: 0.96, 0.99, 1.02 ms at n = 324, 7.2, 6.8, 7.5 at 1875, 7.7,
+// 7.5, 8.2 at 2048 (CS = 4: 6.9), 31.0, 25.5, 26.8 at 6144.
 
 // The block at rows r0 .. r0 + 15 and columns r0 - 16 .. r0 - 1 (first: the column
 // s alone), by one wavefront: the previous reflector from the right, B - z v^H; the

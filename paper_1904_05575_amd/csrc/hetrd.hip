@@ -357,16 +357,6 @@ __global__ __launch_bounds__(COL_THREADS) void k_trd_col(
   }
 }
 
-// Sum over the 16 lanes of each row of the wavefront (DPP within rows); every
-// lane of a row gets its row's total.
-BSE_DEV double row16_sum(double v) {
-  v += dpp_d<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp_d<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp_d<0x141>(v);  // row_half_mirror
-  v += dpp_d<0x140>(v);  // row_mirror
-  return v;
-}
-
 // Reflector c from the column kernel's partials, then the Hermitian product
 // S v over the lower triangle of the trailing matrix (rows and columns c+1..n-1)
 // in HT x HT tiles.  Persistent blocks (at most one per compute unit) take
@@ -587,8 +577,8 @@ __global__ __launch_bounds__(HV_THREADS) void k_trd_hemv(
         if (ok && strict) ca = cadd(ca, cmulc(sv, vr));
       }
     }
-    ca.x = row16_sum(ca.x);
-    ca.y = row16_sum(ca.y);
+    ca.x = row_sum(ca.x);
+    ca.y = row_sum(ca.y);
     if (lr == 0 && cj0 + jl < n) {
       Y[(int64_t)(ycs + I) * N + cj0 + jl] = ca;
       pbl = cadd(pbl, cmulc(ca, vj));
@@ -609,8 +599,8 @@ __global__ __launch_bounds__(HV_THREADS) void k_trd_hemv(
       double2 rs = zero;
 #pragma unroll
       for (int q = 0; q < 4; ++q) rs = cadd(rs, rpart[part + 16 * q][row]);
-      rs.x = row16_sum(rs.x);
-      rs.y = row16_sum(rs.y);
+      rs.x = row_sum(rs.x);
+      rs.y = row_sum(rs.y);
       if (part == 0 && rb0 + row < n) {
         Y[(int64_t)row_slot(I) * N + rb0 + row] = rs;
         pbl = cadd(pbl, cmulc(rs, vrow[ub][row]));

@@ -307,8 +307,11 @@ bse_status bse_pair_elements(const bse_orb_desc* d, const void* C, const int32_t
   if (!C || !kpg || !Mcv || !Mvv || !Mcc) return BSE_ERR_ARG;
   if (full && (!mkg || !Ncv || !Nvc)) return BSE_ERR_ARG;
   const int nv = d->nv, nc = d->nc, ng = d->ng, nkb = d->nkb, nbt = nv + nc;
+  // The limits of the interface, which are narrower than the kernel's own (any number of K,
+  // in parts of PG_ROWS, while a k-point's offsets fit in 32 bits; PG_MAXKINDS pieces of
+  // five bands): 160 KB for the coefficients of two k-points, 24 blocks of 4 x 4 bands.
+  // They bound the kinds and offsets here too.
   if ((size_t)2 * nbt * nkb * sizeof(double2) > PG_LDS) return BSE_ERR_ARG;
-  // at most 24 blocks of 4 x 4 bands in one launch
   const int64_t v4 = (nv + 3) / 4, c4 = (nc + 3) / 4;
   if (v4 * v4 + c4 * c4 + (full ? 3 : 1) * v4 * c4 > PG_MAXKINDS) return BSE_ERR_ARG;
   PgKinds ks{};

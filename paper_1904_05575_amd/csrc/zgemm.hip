@@ -203,10 +203,10 @@ int tile_edge(const ZgemmParams& p, int batch) {
 
 }  // namespace
 
-// The products are bound by the matrix cores (about 50 TFLOP/s of FP64 products issued
-// in every form), so Gauss's three products in place of four are a quarter less
-// time where the third accumulator leaves enough wavefronts: 64-edge tiles take eight
-// wavefronts of 16 x 32 (48 accumulator registers).  At N = 6144, four products on four
+// Every form issues its FP64 products at about 50 TFLOP/s (a loop of the same instruction
+// on registers alone reaches 47, a library product of random matrices 72 to 75), so
+// Gauss's three products in place of four are a quarter less time where the third
+// accumulator leaves enough wavefronts: 64-edge tiles take eight of 16 x 32 (48 accumulator registers).  At N = 6144, four products on four
 // wavefronts of 32 x 32 / three on the same / three on eight: U (A+B) 18.3 / 22.3 / 14.1
 // ms, its product with U^H 6.1 / 7.3 / 4.6 ms, the Cholesky updates 9.9 / 12.8 / 7.3 ms
 // (N = 2000: 0.76 / 0.85 / 0.55, 0.49 / 0.39 / 0.32, 0.59 / 0.65 / 0.52 ms); tiles of
