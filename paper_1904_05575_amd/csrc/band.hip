@@ -59,6 +59,9 @@ constexpr int DIRECT_ROWS = 64;   // panels with fewer rows are factored column 
 constexpr double SERIES_MAX = 2e-6;
 constexpr double fourth(double x) { return x * x * x * x; }
 static_assert(8 * fourth(1.5 * BW * SERIES_MAX) < 1.1e-16, "the series is exact to rounding");
+// Squared norm up to which a column takes H = I: that of the smallest normal number, whose
+// reciprocal is still finite.
+constexpr double COLUMN_ZERO = 2.2250738585072014e-308;
 constexpr int LDT = BW + 1;       // padded row of a 16 x 16 tile in LDS
 constexpr int ABS = 2 * BW + 2;   // band storage per column: 2 BW diagonals, the probe, one spare
                                   // (in LDS a row of the band then steps by 2 BW + 1 values, over
@@ -217,7 +220,7 @@ struct StepShare {  // values of the current elimination step, two steps' buffer
 // row-major), by the block's first 256 threads, each with one element of the
 // matrix and one of the identity beside it; one barrier per column.  L and Li:
 // LDS, rows of LDT.  Returns false (uniformly) when a pivot is not above tol
-// times its diagonal.
+// times its diagonal, or so small that the reciprocals below would overflow.
 BSE_DEV bool chol_inv(const double2* G, double2* L, double2* Li, double* dg, StepShare& sh,
                       double tol) {
   const int e = threadIdx.x & 255, i = e >> 4, j = e & 15;
@@ -237,7 +240,7 @@ BSE_DEV bool chol_inv(const double2* G, double2* L, double2* Li, double* dg, Ste
     const int cur = s & 1, nxt = cur ^ 1;
     const double p = sh.col[cur][s].x;
     const double2 ci = sh.col[cur][i];
-    ok = ok && p > tol * G[s * BW + s].x;
+    ok = ok && p > tol * G[s * BW + s].x && p > COLUMN_ZERO;
     if (on && i > s) {
       const double2 l = cneg(cscale(ci, fast_rcp(p)));
       if (j > s) v = cfma(l, sh.row[cur][0][j], v);
@@ -292,10 +295,10 @@ __global__ __launch_bounds__(64 * NW) void k_band_chol(BandArgs a, BandFirst f, 
     pt[c] = p.M[min(row, n - 1) + (int64_t)(j0 + hi + 4 * c) * p.ld];
   // the partials come from k_band_w over rows j0 .. (t = 0: the first panel)
   sum_partials<NW>(p.g1, panel_blocks(n - j0), G, tmp);
-  // every column zero: nothing to reflect
+  // every column zero, as a reflector takes it: nothing to reflect
   bool zero = true;
 #pragma unroll
-  for (int s = 0; s < BW; ++s) zero = zero && G[s * BW + s].x == 0.0;
+  for (int s = 0; s < BW; ++s) zero = zero && G[s * BW + s].x <= COLUMN_ZERO;
   if (zero) {
     if (bx == 0 && tid == 0) p.ctl[0] = 2;
     return;
@@ -400,7 +403,7 @@ BSE_DEV void panel_small(const BandProb& p, int k, int m, double2* xcol, double2
     xn = row_sum(xn);
     const double nn = cabs2(al) + xn;
     double2 tau = czero(), scal = czero(), beta = al;
-    if (xn != 0.0 && nn > 1e-280) {
+    if (xn != 0.0 && nn > COLUMN_ZERO) {
       const double b = -copysign(sqrt(nn), al.x);
       beta = make_double2(b, 0.0);
       tau = make_double2((b - al.x) / b, -al.y / b);
@@ -502,7 +505,7 @@ BSE_DEV void panel_direct(const BandProb& p, int k, int m, double2* sums, double
     const double2 al = col(j, j);
     const double xn2 = sv[j].x, nn = cabs2(al) + xn2;
     double2 tau = czero(), scal = czero(), beta = al;
-    if (xn2 != 0.0 && nn > 1e-280) {
+    if (xn2 != 0.0 && nn > COLUMN_ZERO) {
       const double b = -copysign(sqrt(nn), al.x);
       beta = make_double2(b, 0.0);
       tau = make_double2((b - al.x) / b, -al.y / b);
@@ -1297,7 +1300,7 @@ BSE_DEV double chase_bulge(double2* ring, double2* ub, int lo, int hi, int r0, b
   const double xn2 = row_sum(lo > 0 ? cabs2(x) : 0.0);
   const double2 al = make_double2(lane_value(x.x, 0), lane_value(x.y, 0));
   const double nn = fma(al.x, al.x, fma(al.y, al.y, xn2));
-  const bool ok = nn > 1e-280 && (xn2 != 0.0 || al.y != 0.0);
+  const bool ok = nn > COLUMN_ZERO && (xn2 != 0.0 || al.y != 0.0);
   const double r = fast_rsq(nn), rb = -copysign(r, al.x), b = nn * rb;
   const double2 dn = make_double2(al.x - b, al.y);
   const double q = fast_rcp(cabs2(dn));
