@@ -59,9 +59,9 @@ constexpr int DIRECT_ROWS = 64;   // panels with fewer rows are factored column 
 constexpr double SERIES_MAX = 2e-6;
 constexpr double fourth(double x) { return x * x * x * x; }
 static_assert(8 * fourth(1.5 * BW * SERIES_MAX) < 1.1e-16, "the series is exact to rounding");
-// Squared norm up to which a column takes H = I: that of the smallest normal number, whose
-// reciprocal is still finite.
-constexpr double COLUMN_ZERO = 2.2250738585072014e-308;
+constexpr double COLUMN_ZERO = 1e-280;  // squared norm up to which a column takes H = I
+constexpr double PIVOT_LEAST = 1e-11;   // of its diagonal: a panel's pivots on the Gram route
+static_assert(COLUMN_ZERO * PIVOT_LEAST > 1e-300, "the pivots' reciprocals are finite");
 constexpr int LDT = BW + 1;       // padded row of a 16 x 16 tile in LDS
 constexpr int ABS = 2 * BW + 2;   // band storage per column: 2 BW diagonals, the probe, one spare
                                   // (in LDS a row of the band then steps by 2 BW + 1 values, over
@@ -220,7 +220,7 @@ struct StepShare {  // values of the current elimination step, two steps' buffer
 // row-major), by the block's first 256 threads, each with one element of the
 // matrix and one of the identity beside it; one barrier per column.  L and Li:
 // LDS, rows of LDT.  Returns false (uniformly) when a pivot is not above tol
-// times its diagonal, or so small that the reciprocals below would overflow.
+// times its diagonal (tol times each diagonal has to be a normal number).
 BSE_DEV bool chol_inv(const double2* G, double2* L, double2* Li, double* dg, StepShare& sh,
                       double tol) {
   const int e = threadIdx.x & 255, i = e >> 4, j = e & 15;
@@ -240,7 +240,7 @@ BSE_DEV bool chol_inv(const double2* G, double2* L, double2* Li, double* dg, Ste
     const int cur = s & 1, nxt = cur ^ 1;
     const double p = sh.col[cur][s].x;
     const double2 ci = sh.col[cur][i];
-    ok = ok && p > tol * G[s * BW + s].x && p > COLUMN_ZERO;
+    ok = ok && p > tol * G[s * BW + s].x;
     if (on && i > s) {
       const double2 l = cneg(cscale(ci, fast_rcp(p)));
       if (j > s) v = cfma(l, sh.row[cur][0][j], v);
@@ -295,18 +295,23 @@ __global__ __launch_bounds__(64 * NW) void k_band_chol(BandArgs a, BandFirst f, 
     pt[c] = p.M[min(row, n - 1) + (int64_t)(j0 + hi + 4 * c) * p.ld];
   // the partials come from k_band_w over rows j0 .. (t = 0: the first panel)
   sum_partials<NW>(p.g1, panel_blocks(n - j0), G, tmp);
-  // every column zero, as a reflector takes it: nothing to reflect
-  bool zero = true;
+  // every column zero, as a reflector takes it: nothing to reflect; some: not by the Gram
+  // route, where the reciprocals of their pivots could overflow
+  double least = G[0].x, most = G[0].x;
 #pragma unroll
-  for (int s = 0; s < BW; ++s) zero = zero && G[s * BW + s].x <= COLUMN_ZERO;
+  for (int s = 1; s < BW; ++s) {
+    least = fmin(least, G[s * BW + s].x);
+    most = fmax(most, G[s * BW + s].x);
+  }
+  const bool zero = most <= COLUMN_ZERO, small = least <= COLUMN_ZERO;
   if (zero) {
     if (bx == 0 && tid == 0) p.ctl[0] = 2;
     return;
   }
-  // a pivot of 1e-11 of its diagonal leaves the first pass orthonormal to about
+  // a pivot of PIVOT_LEAST of its diagonal leaves the first pass orthonormal to about
   // 1e-5, which the second pass squares away (orthonormality alone: the panel's own
   // residual is Q1's to keep, below)
-  const bool ok = chol_inv(G, L, Li, dg, sh, 1e-11);
+  const bool ok = !small && chol_inv(G, L, Li, dg, sh, PIVOT_LEAST);
   if (bx == 0 && tid == 0) p.ctl[0] = ok ? 0 : 1;
   if (!ok) return;
   if (bx == 0 && tid < 256) p.sm[256 + tid] = L[(tid >> 4) * LDT + (tid & 15)];

@@ -150,12 +150,12 @@ namespace {
 // thread keeps two elements of the block and two of the identity, and a step's
 // pivot row and column go through LDS with one barrier.  (A forward substitution
 // of the columns, one per thread, would be a second chain as long: 37-40 us a
-// panel with it, 17 without.)  The product with the explicit inverse leaves a residual
-// A12 - U11^H X of the order u cond(U11) ||A12||, so it is taken once more for that
-// residual, which leaves u ||A12|| as the substitution does.  Block 0 stores U11 into u11 (panel j0 / CH_NB holds CH_NB x
-// CH_NB entries), not into A: the other blocks may still be reading A11 when
-// block 0 is done.  k_potrf_store moves every U11 into A once the factorisation is
-// complete.
+// panel with it, 18 with one product, 21 with the second.)  The product with the
+// explicit inverse leaves a residual A12 - U11^H X of the order u cond(U11) ||A12||, so it
+// is taken once more for that residual, which leaves u ||A12|| as the substitution does.
+// Block 0 stores U11 into u11 (panel j0 / CH_NB holds CH_NB x CH_NB entries), not into A:
+// the other blocks may still be reading A11 when block 0 is done.  k_potrf_store moves
+// every U11 into A once the factorisation is complete.
 constexpr int PCOLS = 64;
 constexpr int PTHREADS = 512;  // four column tiles of 16, two row tiles of 16
 BSE_DEV void potrf_panel_dev(double2* __restrict__ A, int64_t ld, int64_t n, int j0, int jb,

@@ -32,8 +32,8 @@ def test_couplings_near_underflow(cut, size):
 
 @pytest.mark.parametrize("scale", [1e-135, 1e-120, 1e120, 1e150])
 def test_scaled_matrices(scale):
-    """The eigenvalues scale with the matrix while the squares of its elements are in
-    range, and so do those of its small panels."""
+    """The eigenvalues scale with the matrix while the squares of its elements are well
+    inside the range of double precision."""
     n = 220
     print(f"[gpu] band reduction, elements of {scale:g}", flush=True)
     a = _random(n, 6)
